@@ -838,9 +838,9 @@ attuner_status qproj_impl(attuner_ctx* c, int32_t n_tok, const void* x, const vo
   const int r_pad = rank > 0 && lora_cols > 0 ? (rank + 15) / 16 * 16 : 0;
   // ranks up to kGemmFusedLoraMaxRank: the GEMM computes t = scale * x A^T
   // itself where its tile hides the work; larger ranks, the GEMV of a few
-  // tokens and the largest tile take a separate down-projection kernel first
+  // tokens and the read-ahead tiles take a separate down-projection kernel first
   float* t_part = nullptr;
-  if (r_pad > 0 && (r_pad > kGemmFusedLoraMaxRank || n_tok <= kGemvMaxTok || !gemm_fuses_lora(n_tok, n_out, hidden))) {
+  if (r_pad > 0 && (n_tok <= kGemvMaxTok || !gemm_fuses_lora(n_tok, n_out, hidden, r_pad))) {
     const size_t part_bytes = (size_t)lora_down_slices(hidden, n_tok) * n_tok * r_pad * sizeof(float);
     attuner_status st = grow(c, c->ws_lora, part_bytes, stream, "LoRA down-projection");
     if (st != ATTUNER_OK) return st;
@@ -1513,7 +1513,7 @@ static attuner_status check_gemm_args(int32_t n_tok, const void* x, int32_t k_di
 // split workspace when the plan splits the k range.
 static attuner_status run_gemm(attuner_ctx* c, int32_t n_tok, const void* x, int32_t k_dim, const void* w,
                                int32_t n_out, GemmEpi epi, void* out, hipStream_t s) {
-  const GemmPlan plan = plan_gemm(n_tok, n_out, k_dim, false);
+  const GemmPlan plan = plan_gemm(n_tok, n_out, k_dim, false, true);
   float* ws = nullptr;
   if (n_tok > kGemvMaxTok && plan.n_split > 1) {
     attuner_status st = grow(c, c->ws_split, (size_t)plan.n_split * n_tok * n_out * sizeof(float), s, "key-split product");

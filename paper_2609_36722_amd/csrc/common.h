@@ -185,6 +185,19 @@ __device__ __forceinline__ void lds_dma16(const void* gaddr, uint32_t lds_base) 
       : "memory");
 }
 
+// One 16-byte-per-lane global -> LDS copy with a wave-uniform 64-bit base in
+// SGPRs and a per-lane 32-bit byte offset (the saddr form): the offsets stay
+// fixed from tile to tile, only the scalar base moves.  The LDS base goes in
+// through an M0-bound input operand, as in lds_dma16.
+__device__ __forceinline__ void lds_dma16_s(const void* sbase, uint32_t voff, uint32_t lds_base) {
+  asm volatile(
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, %1"
+      :
+      : "v"(voff), "s"(sbase), "{m0}"(lds_base)
+      : "memory");
+}
+
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) char*)p);
 }

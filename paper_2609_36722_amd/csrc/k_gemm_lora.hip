@@ -9,9 +9,11 @@
 // operands are K-contiguous in memory ([rows][hidden]), so tiles go to LDS
 // without a transpose.  Workgroup tile BN (features) x BM (tokens) x 64 (k),
 // 32x32x16 MFMAs, fp32 accumulation, the operand tiles copied global -> LDS
-// by the DMA form of the load.  Two kernels: gemm_lora_kernel (one wave per
-// wave tile) and gemm_kg2_kernel (96 x 64 wave tiles, two groups of waves on
-// alternate k-steps).  At suffix sizes the operand ingest per CU is the
+// by the DMA form of the load.  Three kernels: gemm_lora_kernel (one wave per
+// wave tile), gemm_kg2_kernel (96 x 64 wave tiles, two groups of waves on
+// alternate k-steps) and gemm_ahead_kernel (one wave per wave tile, operand
+// fragments read one k-step ahead; plain products and those whose low-rank t
+// a kernel of its own computes).  At suffix sizes the operand ingest per CU is the
 // ceiling (measured on gfx950: about 58 GB/s per CU, 15 TB/s out of the L2s,
 // the same rate hipBLASLt's kernels reach on these shapes), so the tile shape
 // is chosen to minimise ingested bytes, M N K 2 (1/BM + 1/BN), while keeping
@@ -568,6 +570,152 @@ __global__ __launch_bounds__(128 * WN * WM, 1) void gemm_kg2_kernel(const bf16_t
   else finish(std::integral_constant<int, 1>{});
 }
 
+// The same product for the largest tiles, with the operand fragments read one
+// k-step ahead.  What bounds these tiles is not a rate but waiting: with 64 KB
+// per k-tile only two fit in LDS, and a ring slot that is free only when its
+// k-tile has been multiplied leaves its refill half a k-tile (about 0.5 us,
+// less than a loaded L2's latency) to land.  Here a wave reads the FN + FM
+// fragments of the next k-step between the MFMAs of the current one, so a slot
+// is free when its last k-step has been read, before that step is multiplied:
+// the refill then has a whole k-tile to land, no MFMA waits for an LDS read
+// issued just before it, and there is one barrier per k-tile.  Copies take a
+// scalar base and a fixed 32-bit lane offset, which leaves the registers for
+// the second set of fragments.  The low-rank term comes from t_part only.
+// Measured against the same tiles without read-ahead (one box, 1024 tokens):
+// 256 x 256 at 4096 -> 24576 236 against 252 us, 128 x 256 252 against 277 us
+// and at 12288 -> 4096 (2 splits) 120 against 143 us; a 256 x 256 workgroup
+// takes 160k shader cycles for 64 k-tiles, 132k of them MFMA issue, and from
+// there the chip's power sets the clock (1.58 GHz with every CU busy, 2.25 GHz
+// on zeros).  Waves are wider in the features' direction where the tile allows
+// it: 2 x 4 waves of 128 x 64 at 256 x 256 read 6 fragments per 8 MFMAs.
+template <int BM, int BN, int WN, int WM, int NST>
+__global__ __launch_bounds__(64 * WN * WM, 1) void gemm_ahead_kernel(const bf16_t* __restrict__ x,
+                                                                    const bf16_t* __restrict__ w, int M, int N, int K,
+                                                                    const bf16_t* __restrict__ b, int rank, int r_pad,
+                                                                    int lora_cols, const float* __restrict__ t_part,
+                                                                    int n_slice, GemmEpi epi, bf16_t* out, int n_mt,
+                                                                    int n_nt, int kt_split) {
+  constexpr int NW = WN * WM;
+  constexpr int TN = BN / WN, TM = BM / WM;
+  constexpr int FN = TN / 32, FM = TM / 32;
+  constexpr int NBLK = (BN + BM) / 8;  // 1 KiB blocks of a k-tile stage
+  constexpr int PW = NBLK / NW;        // copies per wave and k-tile
+  static_assert(TN % 32 == 0 && TM % 32 == 0 && NBLK % NW == 0 && (NST - 1) * PW <= 63, "bad wave layout");
+  constexpr int STAGE = (BN + BM) * kChunksPerRow;
+  __shared__ u32x4 lds[NST * STAGE];
+
+  // tile order and key split as in gemm_lora_kernel
+  const int total = n_mt * n_nt;
+  const int per_xcd = total >> 3;
+  const int split = kt_split > 0 ? (int)blockIdx.x / total : 0;
+  int lin = kt_split > 0 ? (int)blockIdx.x % total : (int)blockIdx.x;
+  if (lin < 8 * per_xcd) lin = (lin & 7) * per_xcd + (lin >> 3);
+  const int in_group = kGroupM * n_nt;
+  const int first_m = (lin / in_group) * kGroupM;
+  const int gm = min(n_mt - first_m, kGroupM);
+  const int mt = first_m + (lin % in_group) % gm;
+  const int nt = (lin % in_group) / gm;
+  const int n0 = nt * BN;
+  const int m0 = mt * BM;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wn = wave / WM;
+  const int wm = wave % WM;
+  const int l32 = lane & 31;
+  const int hi = lane >> 5;
+  const int kt0 = split * kt_split;
+  const int n_kt = kt_split > 0 ? min(K / BK - kt0, kt_split) : K / BK;
+  const uint32_t lds0 = lds_addr(lds);
+
+  // Copy j of this wave moves block wave + NW j: rows 8 (wave + NW j) .. + 7
+  // of the stage, W's first (whole blocks of one operand: BN % 8 == 0).
+  const bf16_t* sbase[PW];
+  uint32_t voff[PW];
+#pragma unroll
+  for (int j = 0; j < PW; ++j) {
+    const int row = 8 * (wave + NW * j) + (lane >> 3);
+    const bool is_w = 8 * (wave + NW * j) < BN;
+    // x rows past the end repeat the last: computed, never stored
+    const int r = is_w ? row : min(m0 + row - BN, M - 1) - m0;
+    sbase[j] = (is_w ? w + (int64_t)n0 * K : x + (int64_t)m0 * K) + (int64_t)kt0 * BK;
+    voff[j] = 2u * ((uint32_t)r * (uint32_t)K + 8u * (uint32_t)swz(row, lane & 7));
+  }
+  auto copy = [&](int j, int kt, int slot) __attribute__((always_inline)) {
+    lds_dma16_s(sbase[j] + (int64_t)kt * BK, voff[j], lds0 + (uint32_t)(slot * STAGE * 16) + 1024u * (wave + NW * j));
+  };
+
+  f32x16 acc[FN][FM];
+#pragma unroll
+  for (int i = 0; i < FN; ++i)
+#pragma unroll
+    for (int j = 0; j < FM; ++j) acc[i][j] = f32x16{};
+
+  // fragments of one k-step: FN of W, then FM of x
+  typedef bf16x8 Frags[FN + FM];
+  Frags f0, f1;
+  auto read = [&](Frags& f, const u32x4* cur, int ks, int e) __attribute__((always_inline)) {
+    const int row = e < FN ? wn * TN + e * 32 + l32 : BN + wm * TM + (e - FN) * 32 + l32;
+    f[e] = as_bf16x8(cur[row * kChunksPerRow + swz(row, 2 * ks + hi)]);
+  };
+  // the MFMAs of `cur`, with the reads of the next k-step (ks of stage `st`)
+  // and (COPY) the refill of slot cslot with tile kt spread between them
+  constexpr int NM = FN * FM, NR = FN + FM;
+  auto phase = [&](Frags& cur, Frags& nxt, const u32x4* st, int ks, auto copy_tag, int kt, int cslot)
+                   __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < NM; ++q) {
+      acc[q / FM][q % FM] = mfma32(cur[q / FM], cur[FN + q % FM], acc[q / FM][q % FM]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = q * NR / NM; u < (q + 1) * NR / NM; ++u) read(nxt, st, ks, u);
+      if constexpr (decltype(copy_tag)::value) {
+#pragma unroll
+        for (int u = q * PW / NM; u < (q + 1) * PW / NM; ++u) copy(u, kt, cslot);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  const std::integral_constant<bool, true> with_copy{};
+  const std::integral_constant<bool, false> no_copy{};
+
+#pragma unroll
+  for (int st = 0; st < NST; ++st)
+    if (st < n_kt) {
+#pragma unroll
+      for (int j = 0; j < PW; ++j) copy(j, st, st);
+    }
+  if (n_kt >= NST) __builtin_amdgcn_s_waitcnt(vmcnt_wait((NST - 1) * PW));
+  else __builtin_amdgcn_s_waitcnt(vmcnt_wait(0));
+  barrier_no_fence();
+#pragma unroll
+  for (int u = 0; u < NR; ++u) read(f0, lds, 0, u);
+
+  int slot = 0, kt = 0;
+  auto tile = [&](auto copy_tag) __attribute__((always_inline)) {
+    const int next = slot + 1 == NST ? 0 : slot + 1;
+    const u32x4* st = lds + slot * STAGE;
+    phase(f0, f1, st, 1, no_copy, 0, 0);
+    phase(f1, f0, st, 2, no_copy, 0, 0);
+    phase(f0, f1, st, 3, no_copy, 0, 0);
+    // this wave has read all of tile kt and its copies of tile kt + 1 have
+    // landed (tiles kt + 2 .. kt + NST - 1 may still fly; the last tiles wait
+    // for all); past the barrier so has everyone, and tile kt's slot takes
+    // tile kt + NST.  After the last tile a stale slot is read and not used.
+    __builtin_amdgcn_s_waitcnt(vmcnt_wait(decltype(copy_tag)::value ? (NST - 2) * PW : 0) & ~(15 << 8));
+    barrier_no_fence();
+    phase(f1, f0, lds + next * STAGE, 0, copy_tag, kt + NST, slot);
+    slot = next;
+    ++kt;
+  };
+  while (kt + NST < n_kt) tile(with_copy);
+  while (kt < n_kt) tile(no_copy);
+
+  if (kt_split > 0) epi.out_f32 += (int64_t)split * M * N;
+  lora_epilogue_store<FN, FM>(acc, n0 + wn * TN, m0 + wm * TM, wm * TM, l32, hi, M, N, b, rank, r_pad, lora_cols,
+                              t_part, n_slice, nullptr, epi, out);
+}
+
 // t = scale * x A^T with MFMAs, as fp32 partial sums per slice of the hidden
 // dimension (slice_w wide: 256 for the few-token GEMV, which has few token
 // blocks to spread, kLoraSliceWide otherwise, so that a GEMM epilogue sums
@@ -679,16 +827,22 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   *reinterpret_cast<u32x2*>(out + m * N + n) = pk;
 }
 
-// rate: the operand ingest per CU the tile model assumes (measured on
-// gfx950; the two-k-group kernel overlaps its MFMAs with the copies best)
+// A tile's cost on a chip with every CU busy.  Tiles of the read-ahead kernel:
+// microseconds per 64-deep k-tile and per workgroup (first k-tiles, epilogue),
+// measured.  The others (rate > 0): the operand ingest per CU the model
+// assumes (measured; the two-k-group kernel overlaps its MFMAs with the copies
+// best).  fuses: the kernel can compute the low-rank t itself.
 struct Tile {
   int bm, bn;
+  bool fuses;
   double rate;
+  double kt_us, wg_us;
 };
-constexpr Tile kTiles[] = {{256, 256, 42e9}, {128, 256, 52e9}, {256, 96, 52e9}, {128, 128, 52e9}, {128, 96, 52e9},
-                           {64, 96, 52e9},   {64, 64, 52e9},   {128, 192, 60e9}, {128, 96, 60e9}};
+constexpr Tile kTiles[] = {{256, 256, false, 0, 1.57, 7}, {256, 192, false, 0, 1.24, 5}, {128, 256, false, 0, 0.88, 4},
+                           {128, 128, false, 0, 0.56, 3}, {128, 64, false, 0, 0.30, 2},  {256, 96, true, 52e9, 0, 0},
+                           {128, 128, true, 52e9, 0, 0},  {128, 96, true, 52e9, 0, 0},   {64, 96, true, 52e9, 0, 0},
+                           {64, 64, true, 52e9, 0, 0},    {128, 192, true, 60e9, 0, 0},  {128, 96, true, 60e9, 0, 0}};
 constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
-
 
 hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, const uint16_t* w, int n_tok, int n_out,
                        int hidden, const uint16_t* a, float scale, const uint16_t* b, int rank, int r_pad,
@@ -702,65 +856,86 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
   ATTUNER_LAUNCH("gemm_kg2_kernel", (gemm_kg2_kernel<BM_, BN_, WN_, WM_, NST_>), dim3((unsigned)grid),       \
                  dim3(128 * (WN_) * (WM_)), stream, x, w, n_tok, n_out, hidden, a, scale, b, rank, r_pad,      \
                  lora_cols, t_part, n_slice, epi, out, (n_tok + (BM_) - 1) / (BM_), n_out / (BN_), kt_split)
+#define ATTUNER_GEMM_AHEAD(BM_, BN_, WN_, WM_, NST_)                                                            \
+  ATTUNER_LAUNCH("gemm_ahead_kernel", (gemm_ahead_kernel<BM_, BN_, WN_, WM_, NST_>), dim3((unsigned)grid),    \
+                 dim3(64 * (WN_) * (WM_)), stream, x, w, n_tok, n_out, hidden, b, rank, r_pad, lora_cols,       \
+                 t_part, n_slice, epi, out, (n_tok + (BM_) - 1) / (BM_), n_out / (BN_), kt_split)
   switch (tile) {
-    case 0: ATTUNER_GEMM(256, 256, 4, 2, 2, true); break;
-    case 1: ATTUNER_GEMM(128, 256, 4, 2, 3, false); break;
-    case 2: ATTUNER_GEMM(256, 96, 3, 4, 3, false); break;
-    case 3: ATTUNER_GEMM(128, 128, 2, 2, 4, false); break;
-    case 4: ATTUNER_GEMM(128, 96, 3, 2, 4, false); break;
-    case 5: ATTUNER_GEMM(64, 96, 3, 2, 5, false); break;
-    case 6: ATTUNER_GEMM(64, 64, 2, 2, 6, false); break;
-    case 7: ATTUNER_GEMM_KG2(128, 192, 2, 2, 3); break;
-    case 8: ATTUNER_GEMM_KG2(128, 96, 1, 2, 4); break;
+    case 0: ATTUNER_GEMM_AHEAD(256, 256, 2, 4, 2); break;
+    case 1: ATTUNER_GEMM_AHEAD(256, 192, 2, 4, 2); break;
+    case 2: ATTUNER_GEMM_AHEAD(128, 256, 4, 2, 3); break;
+    case 3: ATTUNER_GEMM_AHEAD(128, 128, 4, 2, 4); break;
+    case 4: ATTUNER_GEMM_AHEAD(128, 64, 2, 2, 6); break;
+    case 5: ATTUNER_GEMM(256, 96, 3, 4, 3, false); break;
+    case 6: ATTUNER_GEMM(128, 128, 2, 2, 4, false); break;
+    case 7: ATTUNER_GEMM(128, 96, 3, 2, 4, false); break;
+    case 8: ATTUNER_GEMM(64, 96, 3, 2, 5, false); break;
+    case 9: ATTUNER_GEMM(64, 64, 2, 2, 6, false); break;
+    case 10: ATTUNER_GEMM_KG2(128, 192, 2, 2, 3); break;
+    case 11: ATTUNER_GEMM_KG2(128, 96, 1, 2, 4); break;
     default: return hipErrorInvalidValue;  // callers keep n_out a multiple of 64: 64x64 always fits
   }
 #undef ATTUNER_GEMM
 #undef ATTUNER_GEMM_KG2
+#undef ATTUNER_GEMM_AHEAD
   return hipGetLastError();
 }
 
 }  // namespace
 
 // Tile and key split of a product, by a model fitted to gfx950 runs.  One
-// workgroup per CU at a time; a workgroup's time is the larger of its operand
-// ingest ((BM + BN) * k-range * 2 bytes at the tile's rate: about 52 GB/s per
-// CU, 42 GB/s for the 256 x 256 tile whose ring holds only two k-tiles, 60
-// GB/s for the two-k-group tiles) and its MFMA work
-// (2 BM BN k-range at about 6 TFLOP/s per CU); a launch takes ceil(workgroups
-// / 256) such rounds plus a fixed 4 us.  Without a low-rank term, and when a
-// tile's workgroups would leave CUs idle, the k range may be split across
-// workgroups: shorter k-loops, paid for by the fp32 partials (split * M * N *
-// 8 bytes written and read at about 4 TB/s) and a 3 us reduce launch.  The
-// plan minimises the model; ties go to the earlier tile and to no split.  On
-// gfx950 it picks the measured fastest plan for the q/k/v projection (6144
-// outputs, hidden 2560 / 4096) at T = 64 (64x64), 256 (64x96), 512 (the
-// two-k-group 128x96), 1024 (the two-k-group 128x192) and 33792 (256x256),
-// and for the o/gate-up/down products of the 4B and 8B layers at 256 and
-// 1024 tokens (e.g. down at 256 tokens: 128x128 in 6 splits, 28.9 us against
-// 46.5 us unsplit).
-GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, bool lora) {
+// workgroup per CU at a time, in rounds of 256, plus a fixed 4 us.  A workgroup
+// of a read-ahead tile costs its measured time per k-tile (plus wg_us); of the
+// other tiles, the larger of its operand ingest ((BM + BN) * k-range * 2 bytes
+// at the tile's rate) and its MFMA work (2 BM BN k-range at about 6 TFLOP/s).
+// With all 256 CUs on large read-ahead tiles the chip is power-limited (a
+// 256 x 256 workgroup of 64 k-tiles: 160k shader cycles always, 101 us at 1.58
+// GHz with 256 CUs busy, 86 us with 192, 76 us with 128, 68 us with 64 or
+// fewer), so a partly filled round of these costs down to 2/3 of a full one;
+// the small tiles wait on memory and gain nothing.  With may_split, and
+// when a tile's workgroups would leave CUs idle, the k range may be split
+// across workgroups: shorter k-loops, paid for by the fp32 partials (split * M
+// * N * 8 bytes written and read at about 6 TB/s) and a 3 us reduce launch.
+// With lora (a low-rank term that a tile may fuse) a tile that does not pays 10
+// us for the down-projection's launch.  The plan minimises the model; ties go to the earlier tile and to no
+// split.  Measured, chosen plan against the plan of the tiles without
+// read-ahead (us): 6000 tokens x 4096 -> 6144 262 (256 x 192) / 325; 1024 x
+// 4096 -> 24576 184 (256 x 192) / 205-225; 1024 x 12288 -> 4096 106 (128 x 256
+// in 2 splits) / 125; 1024 x 4096 -> 4096 42 (128 x 128) / 49; 256 x 9728 ->
+// 2560 24.7 (128 x 64 in 3) / 28.1; 256 x 4096 -> 2560 15.4 (128 x 64 in 3) /
+// 19.8.  The two-k-group tiles stay ahead at 6144 outputs of 512 (128 x 96,
+// 29.9 against 32.8) and 1024 tokens (128 x 192, 50.7 against 53.7).
+GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, bool lora, bool may_split) {
   constexpr double kMfmaPerCu = 6e12, kFixed = 4e-6;
-  constexpr double kPartBw = 4e12, kReduceLaunch = 3e-6;
+  constexpr double kPartBw = 6e12, kReduceLaunch = 3e-6, kLoraDown = 10e-6;
+  constexpr int kCUs = 256;
   constexpr int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
+  // time of a round with n of the 256 CUs busy, in rounds with all busy
+  const auto round_of = [](const Tile& tl, int64_t n) {
+    return tl.rate == 0 && tl.bm * tl.bn > 128 * 128 ? 1.0 - std::min(kCUs - n, (int64_t)192) / 576.0 : 1.0;
+  };
   const int n_kt = k_dim / BK;
   GemmPlan best{-1, 1, 0};
   double best_t = 0.0;
   for (int i = 0; i < kNumTiles; ++i) {
-    if (n_out % kTiles[i].bn != 0) continue;
-    const int64_t tiles = (int64_t)((n_tok + kTiles[i].bm - 1) / kTiles[i].bm) * (n_out / kTiles[i].bn);
-    const double rate = kTiles[i].rate;
+    const Tile& tl = kTiles[i];
+    if (n_out % tl.bn != 0) continue;
+    const int64_t tiles = (int64_t)((n_tok + tl.bm - 1) / tl.bm) * (n_out / tl.bn);
     for (int s : kSplits) {
       // splits only add workgroups where the tiles alone leave CUs idle
-      if (s > 1 && (lora || n_kt < 4 * s || tiles >= 256)) break;
+      if (s > 1 && (!may_split || n_kt < 4 * s || tiles >= kCUs)) break;
       const int kts = (n_kt + s - 1) / s;
       const int used = (n_kt + kts - 1) / kts;  // splits that hold k-tiles
       // fp32 partials of every split: bounded, so that a reserved workspace holds any plan
       if (used > 1 && (int64_t)used * n_tok * n_out * 4 > kGemmSplitWsMaxBytes) break;
-      const int64_t wgs = tiles * used;
+      const int64_t wgs = tiles * used, rest = wgs % kCUs;
       const double k_range = (double)kts * BK;
-      const double per_wg = std::max((kTiles[i].bm + kTiles[i].bn) * k_range * 2 / rate,
-                                     2.0 * kTiles[i].bm * kTiles[i].bn * k_range / kMfmaPerCu);
-      double t = (double)((wgs + 255) / 256) * per_wg + kFixed;
+      const double k_time = tl.rate > 0 ? std::max((tl.bm + tl.bn) * k_range * 2 / tl.rate,
+                                                   2.0 * tl.bm * tl.bn * k_range / kMfmaPerCu)
+                                        : kts * tl.kt_us * 1e-6;
+      double t = kFixed + (double)((wgs + kCUs - 1) / kCUs) * tl.wg_us * 1e-6 +
+                 k_time * ((double)(wgs / kCUs) + (rest > 0 ? round_of(tl, rest) : 0.0));
+      if (lora && !tl.fuses) t += kLoraDown;
       if (used > 1) t += (double)used * n_tok * n_out * 8 / kPartBw + kReduceLaunch;
       if (best.tile < 0 || t < best_t * (1.0 - 1e-9)) {
         best = GemmPlan{i, used, used > 1 ? kts : 0};
@@ -780,8 +955,8 @@ hipError_t launch_gemm_any(const uint16_t* x, const uint16_t* w, int n_tok, int 
   if (n_tok <= kGemvMaxTok)
     return launch_gemv(x, w, n_tok, n_out, hidden, b, rank, r_pad, lora_cols, t_part, epi, out, stream);
   const int n_slice = lora_down_slices(hidden, n_tok);
-  const GemmPlan pl = plan ? *plan : plan_gemm(n_tok, n_out, hidden, r_pad > 0);
-  if (pl.tile < 0) return hipErrorInvalidValue;
+  const GemmPlan pl = *plan;
+  if (pl.tile < 0 || (r_pad > 0 && t_part == nullptr && !kTiles[pl.tile].fuses)) return hipErrorInvalidValue;
   const int tiles = ((n_tok + kTiles[pl.tile].bm - 1) / kTiles[pl.tile].bm) * (n_out / kTiles[pl.tile].bn);
   if (pl.n_split <= 1)
     return launch_tile(pl.tile, 0, tiles, x, w, n_tok, n_out, hidden, a, scale, b, rank, r_pad, lora_cols, t_part,
@@ -799,19 +974,31 @@ hipError_t launch_gemm_any(const uint16_t* x, const uint16_t* w, int n_tok, int 
 
 }  // namespace
 
-// The 256 x 256 tile's eight waves keep its MFMAs busy, so the redundant
-// down-projection (every feature tile of the adapted columns computes t for
-// its tokens) shows in full there: at 5368 tokens x 4096 -> 6144 (rank 16)
-// 268 us fused against 244 us for lora_down_kernel + the GEMM reading t.  The
-// other tiles hide it (1024 tokens, rank 32: 63.6 us fused, 67.4 separate).
-bool gemm_fuses_lora(int n_tok, int n_out, int hidden) {
-  return plan_gemm(n_tok, n_out, hidden, true).tile != 0;
+namespace {
+
+// No key split here: the caller has no workspace for it.  Above
+// kGemmFusedLoraMaxRank the down-projection is a launch of its own whatever
+// the tile.
+GemmPlan plan_lora(int n_tok, int n_out, int hidden, int r_pad) {
+  return plan_gemm(n_tok, n_out, hidden, r_pad > 0 && r_pad <= kGemmFusedLoraMaxRank, false);
+}
+
+}  // namespace
+
+// Tiles that keep their MFMAs busy would show the redundant down-projection
+// (every feature tile of the adapted columns computes t for its tokens) in
+// full: at 5368 tokens x 4096 -> 6144 (rank 16) a fusing 256 x 256 tile took
+// 268 us against 244 us for lora_down_kernel + the GEMM reading t.  The
+// smaller tiles hide it (1024 tokens, rank 32: 63.6 us fused, 67.4 separate).
+bool gemm_fuses_lora(int n_tok, int n_out, int hidden, int r_pad) {
+  const GemmPlan pl = plan_lora(n_tok, n_out, hidden, r_pad);
+  return r_pad <= kGemmFusedLoraMaxRank && (pl.tile < 0 || kTiles[pl.tile].fuses);
 }
 
 hipError_t launch_gemm_lora(const uint16_t* x, const uint16_t* w, int n_tok, int n_out, int hidden,
                             const uint16_t* a, float scale, const uint16_t* b, int rank, int r_pad, int lora_cols,
                             const float* t_part, uint16_t* out, hipStream_t stream) {
-  const GemmPlan pl = plan_gemm(n_tok, n_out, hidden, true);  // no key split here
+  const GemmPlan pl = plan_lora(n_tok, n_out, hidden, r_pad);
   return launch_gemm_any(x, w, n_tok, n_out, hidden, a, scale, b, rank, r_pad, lora_cols, t_part,
                          GemmEpi{kEpiBf16, nullptr, nullptr}, out, &pl, nullptr, stream);
 }

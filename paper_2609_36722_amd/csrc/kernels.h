@@ -62,9 +62,10 @@ hipError_t launch_gather(const int32_t* table_dev, int64_t n_entries, const uint
 // dimension: t_part[lora_down_slices(hidden, n_tok)][n_tok][r_pad]; ranks
 // rank .. r_pad-1 are zero.  The slice count never exceeds that of one token.
 int lora_down_slices(int hidden, int n_tok);
-// Whether the projection GEMM of this shape computes t itself (rank <=
-// kGemmFusedLoraMaxRank); otherwise launch_lora_down runs first.
-bool gemm_fuses_lora(int n_tok, int n_out, int hidden);
+// Whether the projection GEMM of this shape and padded rank computes t itself
+// (rank <= kGemmFusedLoraMaxRank, and a tile that fuses it); otherwise
+// launch_lora_down runs first.
+bool gemm_fuses_lora(int n_tok, int n_out, int hidden, int r_pad);
 hipError_t launch_lora_down(const uint16_t* x, const uint16_t* a, int n_tok, int hidden, int rank, int r_pad,
                             float scale, float* t_part, hipStream_t stream);
 
@@ -95,13 +96,15 @@ struct GemmEpi {
 // Tile (index into the launcher's tile list) and key split of a product:
 // n_split > 1 splits the k range into chunks of kt_split 64-wide k-tiles and
 // needs a workspace of n_split * n_tok * n_out floats (never with a low-rank
-// term).  plan_gemm picks both by the ingest cost model.
+// term).  plan_gemm picks both by a cost model: lora, that a tile which does
+// not fuse the down-projection costs a launch more; may_split, that the caller
+// has the workspace.
 struct GemmPlan {
   int tile;
   int n_split;
   int kt_split;
 };
-GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, bool lora);
+GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, bool lora, bool may_split);
 hipError_t launch_gemm(const uint16_t* x, const uint16_t* w, int n_tok, int n_out, int k_dim, GemmEpi epi,
                        uint16_t* out, const GemmPlan& plan, float* split_ws, hipStream_t stream);
 

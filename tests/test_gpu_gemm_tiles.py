@@ -1,0 +1,65 @@
+"""GPU parity of the read-ahead GEMM tiles at the sizes where they can go
+wrong: token counts one past or one short of a tile, key ranges of few
+64-deep k-tiles (fewer than or just past the ring), split ranges whose last
+part is short, and the low-rank term read from the down-projection kernel's
+partials.  The reference is the fp64 product of the same bf16 operands; the
+bar is the one of a bf16-stored step (tests/_tol.py)."""
+
+import math
+
+import pytest
+import torch
+
+from tests._tol import assert_intermediate_close
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from paper_2609_36722_amd.api import Context, ModelCfg
+
+
+def _normal(gen, *shape, std=1.0):
+    return torch.randn(*shape, generator=gen, device="cuda").mul_(std).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("T,K,N,res", [
+    (2049, 1024, 4096, True),    # 256 x 256, one token past eight tiles
+    (1000, 2048, 9216, False),   # 256 x 192, ragged last token tile
+    (1025, 512, 4096, True),     # 128 x 256, eight k-tiles in a ring of three
+    (769, 4096, 2560, True),     # 128 x 256 in 3 splits of 22, 22 and 20 k-tiles
+    (257, 4096, 9216, False),    # 128 x 128, one token past two tiles
+    (2049, 512, 512, True),      # 128 x 64, eight k-tiles in a ring of six
+    (190, 2560, 2048, True),     # 128 x 64 in 4 splits of 10 k-tiles
+    (1500, 2752, 256, True),     # 128 x 64 in 4 splits, the last one short (43 k-tiles)
+])
+def test_read_ahead_tiles(T, K, N, res):
+    print(f"[case] linear T={T} K={K} N={N} residual={res}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + K + N)
+    x, w = _normal(g, T, K), _normal(g, N, K, std=1 / math.sqrt(K))
+    r = _normal(g, T, N) if res else None
+    out = torch.empty(T, N, dtype=torch.bfloat16, device="cuda")
+    with Context(ModelCfg(n_layers=1, hidden=256), pool_pages=0) as ctx:
+        ctx.linear(x, w, out, residual=r)
+        torch.cuda.synchronize()
+    ref = x.double() @ w.double().t() + (r.double() if res else 0)
+    assert_intermediate_close(out.double().cpu().numpy(), ref.cpu().numpy(), "linear")
+
+
+@pytest.mark.parametrize("T,H,rank", [(1100, 2560, 33), (2500, 4096, 0), (2500, 4096, 16), (300, 4096, 64), (257, 2560, 0)])
+def test_read_ahead_projection(T, H, rank):
+    # rank 0 and ranks above the fused limit take the read-ahead tiles; at
+    # 2500 tokens the small ranks do too, with t from the separate kernel
+    print(f"[case] qproj T={T} H={H} rank={rank}", flush=True)
+    nq, n, scale = 4096, 6144, 0.5
+    g = torch.Generator(device="cuda").manual_seed(T + H + rank)
+    x, w = _normal(g, T, H), _normal(g, n, H, std=1 / math.sqrt(H))
+    a = _normal(g, rank, H, std=1 / math.sqrt(H)) if rank else None
+    b = _normal(g, nq, rank) if rank else None
+    out = torch.empty(T, n, dtype=torch.bfloat16, device="cuda")
+    with Context(ModelCfg(n_layers=1, hidden=H), pool_pages=0) as ctx:
+        ctx.qproj_lora(x, w, a, b, rank, scale, nq, out)
+        torch.cuda.synchronize()
+    ref = x.double() @ w.double().t()
+    if rank:
+        ref[:, :nq] += scale * (x.double() @ a.double().t()) @ b.double().t()
+    assert_intermediate_close(out.double().cpu().numpy(), ref.cpu().numpy(), "qkv")
