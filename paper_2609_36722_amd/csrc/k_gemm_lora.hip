@@ -35,6 +35,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "attuner.h"
 
 namespace attuner {
 
@@ -58,12 +59,15 @@ __device__ __forceinline__ void lora_epilogue_store(f32x16 (&acc)[FN][FM], int n
                                                     int l32, int hi, int M, int N, const bf16_t* __restrict__ b,
                                                     int rank, int r_pad, int lora_cols,
                                                     const float* __restrict__ t_part, int n_slice,
-                                                    const float* t_lds, const GemmEpi& epi, bf16_t* out) {
+                                                    const float* t_lds, const GemmEpi& epi, bf16_t* out,
+                                                    const u32x4 (*b_pre)[2] = nullptr) {
   if (r_pad > 0 && n_base < lora_cols) {
     const int64_t slice_stride = (int64_t)M * r_pad;
     // B rows as 16-byte loads when they are whole 16-byte runs
     const bool b_vec = (rank & 7) == 0 && (reinterpret_cast<uintptr_t>(b) & 15) == 0;
-    for (int ks = 0; ks < r_pad; ks += 16) {
+#pragma unroll
+    for (int ks = 0; ks < ATTUNER_MAX_RANK; ks += 16) {
+      if (ks >= r_pad) break;
       bf16x8 th[FM], tl[FM];
 #pragma unroll
       for (int j = 0; j < FM; ++j) {
@@ -102,7 +106,9 @@ __device__ __forceinline__ void lora_epilogue_store(f32x16 (&acc)[FN][FM], int n
         const int n = nb + l32;
         bf16x8 a;
         const int j0 = ks + 8 * hi;  // this lane's 8 ranks j0 .. j0 + 7 of B row n
-        if (b_vec) {
+        if (b_pre != nullptr && ks < kGemmFusedLoraMaxRank) {
+          a = as_bf16x8(b_pre[i][ks < kGemmFusedLoraMaxRank ? ks / 16 : 0]);
+        } else if (b_vec) {
           // rank % 8 == 0: the 8 ranks are all below rank or all past it
           u32x4 v = u32x4{0u, 0u, 0u, 0u};
           if (j0 < rank) v = *reinterpret_cast<const u32x4*>(b + (int64_t)n * rank + j0);
@@ -167,7 +173,7 @@ __device__ __forceinline__ void lora_epilogue_store(f32x16 (&acc)[FN][FM], int n
 // one barrier per k-tile.  A k-tile stage is (BN + BM) rows of 128 bytes,
 // moved as 1 KiB blocks of 8 rows (lane i -> row 8 blk + i / 8, physical
 // chunk i % 8, holding the logical chunk the swizzle maps there).
-template <int BM, int BN, int WN, int WM, int NST, bool ILV>
+template <int BM, int BN, int WN, int WM, int NST>
 __global__ __launch_bounds__(64 * WN * WM, 1) void gemm_lora_kernel(const bf16_t* __restrict__ x,
                                                                    const bf16_t* __restrict__ w, int M, int N, int K,
                                                                    const bf16_t* __restrict__ a, float scale,
@@ -209,7 +215,7 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void gemm_lora_kernel(const bf16_t
   const int m0 = mt * BM;
 
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int wn = wave / WM;
   const int wm = wave % WM;
   const int l32 = lane & 31;
@@ -229,12 +235,14 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void gemm_lora_kernel(const bf16_t
   // one wave that holds its x fragments accumulates t^T = A x^T next to its
   // main MFMAs.  t then goes through LDS to the epilogue.
   const bool fused = t_part == nullptr && r_pad > 0 && n0 < lora_cols;
-  f32x16 tacc[FM];
-#pragma unroll
-  for (int j = 0; j < FM; ++j) tacc[j] = f32x16{};
+  static_assert(FM <= WN, "at most one t block per wave");
+  f32x16 tacc = f32x16{};
 
-  auto kloop = [&](auto la_tag) __attribute__((always_inline)) {
+  // la_tag: stage A's rows; tj_tag: the token block whose t this wave
+  // accumulates (-1: none)
+  auto kloop = [&](auto la_tag, auto tj_tag) __attribute__((always_inline)) {
     constexpr bool LA = decltype(la_tag)::value;
+    constexpr int TJ = decltype(tj_tag)::value;
     constexpr int NBLK = (BN + BM + (LA ? kLoraRows : 0)) / 8;
     constexpr int PW = (NBLK + NW - 1) / NW;  // DMA instructions per wave per stage
     static_assert((NST - 2) * PW <= 63, "vmcnt range");
@@ -266,9 +274,6 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void gemm_lora_kernel(const bf16_t
 #pragma unroll
       for (int j = 0; j < PW; ++j) lds_dma16(src[j] + kt * BK, lds0 + (uint32_t)(st * STAGE * 16) + doff[j]);
     }
-    // t block j (32 tokens) is accumulated by the wave column wn == j % WN
-    // of the wave row that holds those tokens: the extra MFMAs spread over
-    // min(FM, WN) wave columns
     int slot = 0, nslot = NST - 1;
     for (int kt = 0; kt < n_kt; ++kt) {
       // own copies of tile kt done, then everyone's; slot nslot (tile kt - 1) is free
@@ -276,15 +281,8 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void gemm_lora_kernel(const bf16_t
       barrier_no_fence();
       const int nk = min(kt + NST - 1, n_kt - 1);
       const u32x4* cur = lds + slot * STAGE;
-      // ILV: the stage's copies are spread over the k-steps (one after
-      // every second MFMA, the rest after the last k-step), so that a wave
-      // whose copies wait for room in the memory pipeline has MFMAs in
-      // flight; otherwise all are issued here
-      int d = ILV ? 0 : PW;
-      if (!ILV) {
 #pragma unroll
-        for (int j = 0; j < PW; ++j) lds_dma16(src[j] + nk * BK, lds0 + (uint32_t)(nslot * STAGE * 16) + doff[j]);
-      }
+      for (int j = 0; j < PW; ++j) lds_dma16(src[j] + nk * BK, lds0 + (uint32_t)(nslot * STAGE * 16) + doff[j]);
 #pragma unroll
       for (int ks = 0; ks < BK / 16; ++ks) {
         const int ch = 2 * ks + hi;
@@ -299,31 +297,15 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void gemm_lora_kernel(const bf16_t
           const int row = BN + wm * TM + j * 32 + l32;
           bfr[j] = as_bf16x8(cur[row * kChunksPerRow + swz(row, ch)]);
         }
-        int q = 0;
 #pragma unroll
         for (int i = 0; i < FN; ++i)
 #pragma unroll
-          for (int j = 0; j < FM; ++j) {
-            acc[i][j] = mfma32(af[i], bfr[j], acc[i][j]);
-            if (ILV && (q & 1) == 1 && d < PW) {
-              __builtin_amdgcn_sched_barrier(0);
-              lds_dma16(src[d] + nk * BK, lds0 + (uint32_t)(nslot * STAGE * 16) + doff[d]);
-              __builtin_amdgcn_sched_barrier(0);
-              ++d;
-            }
-            ++q;
-          }
-        if (LA && wn < FM) {
+          for (int j = 0; j < FM; ++j) acc[i][j] = mfma32(af[i], bfr[j], acc[i][j]);
+        if constexpr (TJ >= 0) {
           const int row = BN + BM + l32;
-          const bf16x8 ar = as_bf16x8(cur[row * kChunksPerRow + swz(row, ch)]);
-#pragma unroll
-          for (int j = 0; j < FM; ++j)
-            if (j % WN == wn) tacc[j] = mfma32(ar, bfr[j], tacc[j]);
+          tacc = mfma32(as_bf16x8(cur[row * kChunksPerRow + swz(row, ch)]), bfr[TJ], tacc);
         }
       }
-#pragma unroll
-      for (int e = 0; e < PW; ++e)
-        if (e >= d) lds_dma16(src[e] + nk * BK, lds0 + (uint32_t)(nslot * STAGE * 16) + doff[e]);
       slot = slot + 1 == NST ? 0 : slot + 1;
       nslot = nslot + 1 == NST ? 0 : nslot + 1;
     }
@@ -333,29 +315,56 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void gemm_lora_kernel(const bf16_t
   };
 
   const float* t_lds = nullptr;
+  // the wave's B rows, requested before the k-loop (whole 16-byte runs only):
+  // read in the epilogue they would cost it a memory latency
+  u32x4 b_pre[FN][2];
+  const bool pre = fused && (rank & 7) == 0 && (reinterpret_cast<uintptr_t>(b) & 15) == 0;
+  if (pre) {
+#pragma unroll
+    for (int i = 0; i < FN; ++i)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int nb = n0 + wn * TN + i * 32, j0 = 16 * q + 8 * hi;
+        b_pre[i][q] = u32x4{0u, 0u, 0u, 0u};
+        if (nb < lora_cols && j0 < rank)
+          b_pre[i][q] = *reinterpret_cast<const u32x4*>(b + (int64_t)(nb + l32) * rank + j0);
+      }
+  }
   if (fused) {
-    kloop(std::integral_constant<bool, true>{});
+    // t block j (32 tokens) is accumulated by the wave column wn == j of the
+    // wave row that holds those tokens.  Each case is a loop of its own: a
+    // branch inside the loop would end a basic block at every k-step, and the
+    // next step's LDS reads could not be issued before it (one layer of 256
+    // tokens x 2560 at rank 16, 27 us of it this product: 84.3 us with the
+    // branch and B read in the epilogue, 80.8 us as it is now).
+    const std::integral_constant<bool, true> la{};
+    if (wn == 0) kloop(la, std::integral_constant<int, 0>{});
+    else if (FM > 1 && wn == 1) kloop(la, std::integral_constant<int, (FM > 1 ? 1 : 0)>{});
+    else kloop(la, std::integral_constant<int, -1>{});
+    static_assert(FM <= 2, "t blocks 0 and 1 only");
     // t^T accumulator: lane holds ranks 8 (v / 4) + 4 hi + v % 4 of token
     // l32 of each 32-token block; staged as fp32 t[token][rank], row stride
     // kLoraRows + 1
     float* ts = reinterpret_cast<float*>(lds);
     barrier_no_fence();
+    if (wn < FM) {
+      const int ml = wm * TM + wn * 32 + l32;
 #pragma unroll
-    for (int j = 0; j < FM; ++j) {
-      if (j % WN != wn) continue;
-      const int ml = wm * TM + j * 32 + l32;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) ts[ml * (kLoraRows + 1) + 8 * (v >> 2) + 4 * hi + (v & 3)] = scale * tacc[j][v];
+      for (int v = 0; v < 16; ++v) ts[ml * (kLoraRows + 1) + 8 * (v >> 2) + 4 * hi + (v & 3)] = scale * tacc[v];
     }
     __syncthreads();
     t_lds = ts;
   } else {
-    kloop(std::integral_constant<bool, false>{});
+    kloop(std::integral_constant<bool, false>{}, std::integral_constant<int, -1>{});
   }
 
   if (kt_split > 0) epi.out_f32 += (int64_t)split * M * N;
-  lora_epilogue_store<FN, FM>(acc, n0 + wn * TN, m0 + wm * TM, wm * TM, l32, hi, M, N, b, rank, r_pad, lora_cols,
-                              t_part, n_slice, t_lds, epi, out);
+  if (pre)
+    lora_epilogue_store<FN, FM>(acc, n0 + wn * TN, m0 + wm * TM, wm * TM, l32, hi, M, N, b, rank, r_pad, lora_cols,
+                                t_part, n_slice, t_lds, epi, out, b_pre);
+  else
+    lora_epilogue_store<FN, FM>(acc, n0 + wn * TN, m0 + wm * TM, wm * TM, l32, hi, M, N, b, rank, r_pad, lora_cols,
+                                t_part, n_slice, t_lds, epi, out);
 }
 
 // The same product with two k-groups of waves.  Each wave holds a 96 x 64
@@ -848,8 +857,8 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
                        int hidden, const uint16_t* a, float scale, const uint16_t* b, int rank, int r_pad,
                        int lora_cols, const float* t_part, int n_slice, GemmEpi epi, uint16_t* out,
                        hipStream_t stream) {
-#define ATTUNER_GEMM(BM_, BN_, WN_, WM_, NST_, ILV_)                                                           \
-  ATTUNER_LAUNCH("gemm_lora_kernel", (gemm_lora_kernel<BM_, BN_, WN_, WM_, NST_, ILV_>), dim3((unsigned)grid), \
+#define ATTUNER_GEMM(BM_, BN_, WN_, WM_, NST_)                                                                 \
+  ATTUNER_LAUNCH("gemm_lora_kernel", (gemm_lora_kernel<BM_, BN_, WN_, WM_, NST_>), dim3((unsigned)grid),       \
                  dim3(64 * (WN_) * (WM_)), stream, x, w, n_tok, n_out, hidden, a, scale, b, rank, r_pad,       \
                  lora_cols, t_part, n_slice, epi, out, (n_tok + (BM_) - 1) / (BM_), n_out / (BN_), kt_split)
 #define ATTUNER_GEMM_KG2(BM_, BN_, WN_, WM_, NST_)                                                             \
@@ -866,11 +875,11 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
     case 2: ATTUNER_GEMM_AHEAD(128, 256, 4, 2, 3); break;
     case 3: ATTUNER_GEMM_AHEAD(128, 128, 4, 2, 4); break;
     case 4: ATTUNER_GEMM_AHEAD(128, 64, 2, 2, 6); break;
-    case 5: ATTUNER_GEMM(256, 96, 3, 4, 3, false); break;
-    case 6: ATTUNER_GEMM(128, 128, 2, 2, 4, false); break;
-    case 7: ATTUNER_GEMM(128, 96, 3, 2, 4, false); break;
-    case 8: ATTUNER_GEMM(64, 96, 3, 2, 5, false); break;
-    case 9: ATTUNER_GEMM(64, 64, 2, 2, 6, false); break;
+    case 5: ATTUNER_GEMM(256, 96, 3, 4, 3); break;
+    case 6: ATTUNER_GEMM(128, 128, 2, 2, 4); break;
+    case 7: ATTUNER_GEMM(128, 96, 3, 2, 4); break;
+    case 8: ATTUNER_GEMM(64, 96, 3, 2, 5); break;
+    case 9: ATTUNER_GEMM(64, 64, 2, 2, 6); break;
     case 10: ATTUNER_GEMM_KG2(128, 192, 2, 2, 3); break;
     case 11: ATTUNER_GEMM_KG2(128, 96, 1, 2, 4); break;
     default: return hipErrorInvalidValue;  // callers keep n_out a multiple of 64: 64x64 always fits
