@@ -942,7 +942,7 @@ attuner_status attuner_reserve(attuner_ctx* c, const attuner_limits* lim) {
   const int64_t widest = std::max(lim->max_out, lim->max_vocab);
   if (st == ATTUNER_OK && T > 0 && widest > 0)
     st = grow(c, c->ws_split,
-              (size_t)std::min<int64_t>(kGemmSplitWsMaxBytes, (int64_t)kMaxGemmSplit * T * widest * 4), s,
+              (size_t)std::min<int64_t>(kGemmSplitWsMaxBytes, (int64_t)kMaxGemmSplit * std::max<int64_t>(T, lim->max_lm_rows) * widest * 4), s,
               "key-split product");
   if (st == ATTUNER_OK && lim->max_lm_rows > 0 && lim->max_vocab > 0)
     st = grow(c, c->ws_logits,
@@ -1513,9 +1513,14 @@ static attuner_status check_gemm_args(int32_t n_tok, const void* x, int32_t k_di
 // split workspace when the plan splits the k range.
 static attuner_status run_gemm(attuner_ctx* c, int32_t n_tok, const void* x, int32_t k_dim, const void* w,
                                int32_t n_out, GemmEpi epi, void* out, hipStream_t s) {
-  const GemmPlan plan = plan_gemm(n_tok, n_out, k_dim, false, true);
+  GemmPlan plan = plan_gemm(n_tok, n_out, k_dim, 0, true);
+  // a split needs a workspace: where it would have to grow on a captured
+  // stream, a product of few tokens runs unsplit
+  if (n_tok <= 32 && plan.n_split > 1 && (size_t)plan.n_split * n_tok * n_out * sizeof(float) > c->ws_split.cap &&
+      capturing(s))
+    plan = plan_gemm(n_tok, n_out, k_dim, 0, false);
   float* ws = nullptr;
-  if (n_tok > kGemvMaxTok && plan.n_split > 1) {
+  if (plan.n_split > 1) {
     attuner_status st = grow(c, c->ws_split, (size_t)plan.n_split * n_tok * n_out * sizeof(float), s, "key-split product");
     if (st != ATTUNER_OK) return st;
     ws = static_cast<float*>(c->ws_split.ptr);

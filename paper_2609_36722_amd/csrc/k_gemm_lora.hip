@@ -650,7 +650,19 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void gemm_ahead_kernel(const bf16_
     sbase[j] = (is_w ? w + (int64_t)n0 * K : x + (int64_t)m0 * K) + (int64_t)kt0 * BK;
     voff[j] = 2u * ((uint32_t)r * (uint32_t)K + 8u * (uint32_t)swz(row, lane & 7));
   }
+  // A few-token tile streams W from memory, each workgroup one 128-byte line of
+  // BN rows at a time.  Started together they would all read the same columns,
+  // which at a power-of-two row stride fall on few memory channels: workgroup
+  // lin starts lin k-tiles further on and wraps (16 tokens x 4096 -> 24576:
+  // 44.7-46.5 us in step, 35.4 staggered; no change at 2560 and 9728).  Larger
+  // token tiles share operand panels in L2 and lose by it (256 x 192 at 6000
+  // tokens x 4096 -> 6144: 263-274 in step, 268-301 staggered).
+  const int kt_first = BM == 32 ? lin % n_kt : 0;
   auto copy = [&](int j, int kt, int slot) __attribute__((always_inline)) {
+    if (BM == 32) {
+      kt += kt_first;
+      kt -= kt >= n_kt ? n_kt : 0;
+    }
     lds_dma16_s(sbase[j] + (int64_t)kt * BK, voff[j], lds0 + (uint32_t)(slot * STAGE * 16) + 1024u * (wave + NW * j));
   };
 
@@ -850,7 +862,8 @@ struct Tile {
 constexpr Tile kTiles[] = {{256, 256, false, 0, 1.57, 7}, {256, 192, false, 0, 1.24, 5}, {128, 256, false, 0, 0.88, 4},
                            {128, 128, false, 0, 0.56, 3}, {128, 64, false, 0, 0.30, 2},  {256, 96, true, 52e9, 0, 0},
                            {128, 128, true, 52e9, 0, 0},  {128, 96, true, 52e9, 0, 0},   {64, 96, true, 52e9, 0, 0},
-                           {64, 64, true, 52e9, 0, 0},    {128, 192, true, 60e9, 0, 0},  {128, 96, true, 60e9, 0, 0}};
+                           {64, 64, true, 52e9, 0, 0},    {128, 192, true, 60e9, 0, 0},  {128, 96, true, 60e9, 0, 0},
+                           {32, 128, false, 0, 0.22, 2},  {32, 64, false, 0, 0.20, 2}};
 constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
 hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, const uint16_t* w, int n_tok, int n_out,
@@ -882,6 +895,8 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
     case 9: ATTUNER_GEMM(64, 64, 2, 2, 6); break;
     case 10: ATTUNER_GEMM_KG2(128, 192, 2, 2, 3); break;
     case 11: ATTUNER_GEMM_KG2(128, 96, 1, 2, 4); break;
+    case 12: ATTUNER_GEMM_AHEAD(32, 128, 4, 1, 4); break;
+    case 13: ATTUNER_GEMM_AHEAD(32, 64, 2, 1, 8); break;
     default: return hipErrorInvalidValue;  // callers keep n_out a multiple of 64: 64x64 always fits
   }
 #undef ATTUNER_GEMM
@@ -905,8 +920,10 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 // when a tile's workgroups would leave CUs idle, the k range may be split
 // across workgroups: shorter k-loops, paid for by the fp32 partials (split * M
 // * N * 8 bytes written and read at about 6 TB/s) and a 3 us reduce launch.
-// With lora (a low-rank term that a tile may fuse) a tile that does not pays 10
-// us for the down-projection's launch.  The plan minimises the model; ties go to the earlier tile and to no
+// With a low-rank term that a tile may fuse, one that does not pays 10 us for
+// the down-projection's launch; the small read-ahead tiles, whose few waves
+// would each sum t's partials for 64 tokens, are left out (one layer of 184
+// tokens x 2560 at rank 64: 59.0 us with 128 x 64, 56.7 with 64 x 96).  The plan minimises the model; ties go to the earlier tile and to no
 // split.  Measured, chosen plan against the plan of the tiles without
 // read-ahead (us): 6000 tokens x 4096 -> 6144 262 (256 x 192) / 325; 1024 x
 // 4096 -> 24576 184 (256 x 192) / 205-225; 1024 x 12288 -> 4096 106 (128 x 256
@@ -914,7 +931,7 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 // 2560 24.7 (128 x 64 in 3) / 28.1; 256 x 4096 -> 2560 15.4 (128 x 64 in 3) /
 // 19.8.  The two-k-group tiles stay ahead at 6144 outputs of 512 (128 x 96,
 // 29.9 against 32.8) and 1024 tokens (128 x 192, 50.7 against 53.7).
-GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, bool lora, bool may_split) {
+GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, bool may_split) {
   constexpr double kMfmaPerCu = 6e12, kFixed = 4e-6;
   constexpr double kPartBw = 6e12, kReduceLaunch = 3e-6, kLoraDown = 10e-6;
   constexpr int kCUs = 256;
@@ -923,12 +940,18 @@ GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, bool lora, bool may_split) {
   const auto round_of = [](const Tile& tl, int64_t n) {
     return tl.rate == 0 && tl.bm * tl.bn > 128 * 128 ? 1.0 - std::min(kCUs - n, (int64_t)192) / 576.0 : 1.0;
   };
+  constexpr double kHbm = 5.5e12;
+  constexpr int64_t kGemvMaxWeights = 20000000;
   const int n_kt = k_dim / BK;
   GemmPlan best{-1, 1, 0};
+  if (n_tok <= kGemvDotMaxTok ||
+      (n_tok <= kGemvMaxTok && (!may_split || (int64_t)n_out * k_dim < kGemvMaxWeights)))
+    return best;
   double best_t = 0.0;
   for (int i = 0; i < kNumTiles; ++i) {
     const Tile& tl = kTiles[i];
-    if (n_out % tl.bn != 0) continue;
+    if (n_out % tl.bn != 0 || (tl.bm == 32) != (may_split && n_tok <= 32)) continue;
+    if (r_pad > 0 && !tl.fuses && tl.bm * tl.bn <= 128 * 128) continue;
     const int64_t tiles = (int64_t)((n_tok + tl.bm - 1) / tl.bm) * (n_out / tl.bn);
     for (int s : kSplits) {
       // splits only add workgroups where the tiles alone leave CUs idle
@@ -942,9 +965,10 @@ GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, bool lora, bool may_split) {
       const double k_time = tl.rate > 0 ? std::max((tl.bm + tl.bn) * k_range * 2 / tl.rate,
                                                    2.0 * tl.bm * tl.bn * k_range / kMfmaPerCu)
                                         : kts * tl.kt_us * 1e-6;
-      double t = kFixed + (double)((wgs + kCUs - 1) / kCUs) * tl.wg_us * 1e-6 +
-                 k_time * ((double)(wgs / kCUs) + (rest > 0 ? round_of(tl, rest) : 0.0));
-      if (lora && !tl.fuses) t += kLoraDown;
+      double t = k_time * ((double)(wgs / kCUs) + (rest > 0 ? round_of(tl, rest) : 0.0));
+      if (tl.bm == 32) t = std::max(t, (double)n_out * k_dim * 2 / (kHbm * std::min(1.0, wgs / (tl.bn == 64 ? 224.0 : 144.0))));
+      t += kFixed + (double)((wgs + kCUs - 1) / kCUs) * tl.wg_us * 1e-6;
+      if (r_pad > 0 && r_pad <= kGemmFusedLoraMaxRank && !tl.fuses) t += kLoraDown;
       if (used > 1) t += (double)used * n_tok * n_out * 8 / kPartBw + kReduceLaunch;
       if (best.tile < 0 || t < best_t * (1.0 - 1e-9)) {
         best = GemmPlan{i, used, used > 1 ? kts : 0};
@@ -961,11 +985,11 @@ hipError_t launch_gemm_any(const uint16_t* x, const uint16_t* w, int n_tok, int 
                            float scale, const uint16_t* b, int rank, int r_pad, int lora_cols, const float* t_part,
                            GemmEpi epi, uint16_t* out, const GemmPlan* plan, float* split_ws, hipStream_t stream) {
   if (n_tok == 0) return hipSuccess;
-  if (n_tok <= kGemvMaxTok)
+  const GemmPlan pl = *plan;
+  if (pl.tile < 0)
     return launch_gemv(x, w, n_tok, n_out, hidden, b, rank, r_pad, lora_cols, t_part, epi, out, stream);
   const int n_slice = lora_down_slices(hidden, n_tok);
-  const GemmPlan pl = *plan;
-  if (pl.tile < 0 || (r_pad > 0 && t_part == nullptr && !kTiles[pl.tile].fuses)) return hipErrorInvalidValue;
+  if ((r_pad > 0 && t_part == nullptr && !kTiles[pl.tile].fuses)) return hipErrorInvalidValue;
   const int tiles = ((n_tok + kTiles[pl.tile].bm - 1) / kTiles[pl.tile].bm) * (n_out / kTiles[pl.tile].bn);
   if (pl.n_split <= 1)
     return launch_tile(pl.tile, 0, tiles, x, w, n_tok, n_out, hidden, a, scale, b, rank, r_pad, lora_cols, t_part,
@@ -985,11 +1009,9 @@ hipError_t launch_gemm_any(const uint16_t* x, const uint16_t* w, int n_tok, int 
 
 namespace {
 
-// No key split here: the caller has no workspace for it.  Above
-// kGemmFusedLoraMaxRank the down-projection is a launch of its own whatever
-// the tile.
+// No key split here: the caller has no workspace for it.
 GemmPlan plan_lora(int n_tok, int n_out, int hidden, int r_pad) {
-  return plan_gemm(n_tok, n_out, hidden, r_pad > 0 && r_pad <= kGemmFusedLoraMaxRank, false);
+  return plan_gemm(n_tok, n_out, hidden, r_pad, false);
 }
 
 }  // namespace

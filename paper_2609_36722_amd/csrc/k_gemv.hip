@@ -293,10 +293,6 @@ __global__ __launch_bounds__(64 * NW) void gemv_mfma_kernel(const bf16_t* __rest
   }
 }
 
-// From this many tokens the matrix-core form (k_dim % 128 == 0, n_out % 16
-// == 0) replaces the dot-product one.
-constexpr int kGemvMfmaMinTok = 9;
-
 // Waves per row pair (measured on the model's projection shapes): one for
 // more than 8 tokens, whose x chunks already fill the loads in flight; else
 // four for long rows (K >= 8192, or K >= 4096 from 4 tokens on), two
@@ -316,7 +312,7 @@ hipError_t launch_gemv(const uint16_t* x, const uint16_t* w, int n_tok, int n_ou
   if (n_tok > kGemvMaxTok || n_out % 8 != 0 || k_dim % 8 != 0 || (r_pad > 0 && t_part == nullptr))
     return hipErrorInvalidValue;
   const int n_slice = lora_down_slices(k_dim, n_tok);
-  if (n_tok >= kGemvMfmaMinTok && k_dim % 128 == 0 && n_out % 16 == 0) {
+  if (n_tok > kGemvDotMaxTok && k_dim % 128 == 0 && n_out % 16 == 0) {
     ATTUNER_LAUNCH("gemv_mfma_kernel", (gemv_mfma_kernel<2, 8>), dim3((unsigned)(n_out / 16)), dim3(512), stream, x, w,
                    n_tok, n_out, k_dim, b, rank, r_pad, lora_cols, t_part, n_slice, epi, out);
     return hipGetLastError();

@@ -96,24 +96,24 @@ struct GemmEpi {
 // Tile (index into the launcher's tile list) and key split of a product:
 // n_split > 1 splits the k range into chunks of kt_split 64-wide k-tiles and
 // needs a workspace of n_split * n_tok * n_out floats (never with a low-rank
-// term).  plan_gemm picks both by a cost model: lora, that a tile which does
-// not fuse the down-projection costs a launch more; may_split, that the caller
-// has the workspace.
+// term).  plan_gemm picks both by a cost model for a low-rank term of padded
+// rank r_pad (0: none); may_split: the caller has the workspace.
 struct GemmPlan {
   int tile;
   int n_split;
   int kt_split;
 };
-GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, bool lora, bool may_split);
+GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, bool may_split);
 hipError_t launch_gemm(const uint16_t* x, const uint16_t* w, int n_tok, int n_out, int k_dim, GemmEpi epi,
                        uint16_t* out, const GemmPlan& plan, float* split_ws, hipStream_t stream);
 
 // The same product for at most kGemvMaxTok tokens as a weight-streaming
 // GEMV (any mode; the low-rank term needs t_part from launch_lora_down);
-// n_out and k_dim multiples of 8.  launch_gemm_lora and launch_gemm route
-// such token counts here; from 9 tokens (k_dim % 128 == 0, n_out % 16 ==
-// 0) the GEMV runs on the matrix cores.
+// n_out and k_dim multiples of 8.  A plan with tile < 0 (plan_gemm's for few
+// tokens) goes here; from 9 tokens (k_dim % 128 == 0, n_out % 16 == 0) the
+// GEMV runs on the matrix cores.
 constexpr int kGemvMaxTok = 16;
+constexpr int kGemvDotMaxTok = 8;  // more tokens: the matrix cores
 
 // Key splits of a plain product: at most kMaxGemmSplit, and their fp32
 // partials (splits x n_tok x n_out x 4 bytes) at most kGemmSplitWsMaxBytes.

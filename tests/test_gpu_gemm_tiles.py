@@ -31,6 +31,9 @@ def _normal(gen, *shape, std=1.0):
     (2049, 512, 512, True),      # 128 x 64, eight k-tiles in a ring of six
     (190, 2560, 2048, True),     # 128 x 64 in 4 splits of 10 k-tiles
     (1500, 2752, 256, True),     # 128 x 64 in 4 splits, the last one short (43 k-tiles)
+    # 32-token tiles: the fewest tokens, 16, one past the GEMV's, a full tile
+    (9, 2560, 8192, True), (16, 9728, 2560, True), (17, 4096, 4096, True), (32, 2560, 2560, False),
+    (31, 1088, 640, True), (12, 512, 40960, False), (17, 64, 64, True),
 ])
 def test_read_ahead_tiles(T, K, N, res):
     print(f"[case] linear T={T} K={K} N={N} residual={res}", flush=True)
@@ -63,3 +66,24 @@ def test_read_ahead_projection(T, H, rank):
     if rank:
         ref[:, :nq] += scale * (x.double() @ a.double().t()) @ b.double().t()
     assert_intermediate_close(out.double().cpu().numpy(), ref.cpu().numpy(), "qkv")
+
+
+def test_few_tokens_capture_without_a_workspace():
+    # 16 tokens x 9728 -> 2560 runs as key splits; on a captured stream whose
+    # context has no split workspace it runs unsplit, and replays
+    print("[case] linear captured, 16 tokens, nothing reserved", flush=True)
+    T, K, N = 16, 9728, 2560
+    g = torch.Generator(device="cuda").manual_seed(5)
+    w = _normal(g, N, K, std=1 / math.sqrt(K))
+    x, out = torch.zeros(T, K, dtype=torch.bfloat16, device="cuda"), torch.empty(T, N, dtype=torch.bfloat16, device="cuda")
+    with Context(ModelCfg(n_layers=1, hidden=256), pool_pages=0) as ctx:
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            ctx.linear(x, w, out)
+        for _ in range(3):
+            x.copy_(_normal(g, T, K))
+            graph.replay()
+            torch.cuda.synchronize()
+            ref = x.double() @ w.double().t()
+            assert_intermediate_close(out.double().cpu().numpy(), ref.cpu().numpy(), "linear")
