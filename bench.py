@@ -650,7 +650,7 @@ def main():
     attn_tflops = attn_f / (attn_kernel_ms * 1e-3) / 1e12          # the attention kernel alone
     attn_call_tflops = attn_f / (kern_ms["attn"] * 1e-3) / 1e12   # attuner_suffix_attn call (+ norm, merge)
     # the projection runs one GEMM kernel per layer (which one: the tile plan)
-    gemm_name = next(k for k in ("gemm_kg2_kernel", "gemm_lora_kernel") if k in ktimes)
+    gemm_name = next(k for k in ("gemm_kg2_kernel", "gemm_ahead_kernel", "gemm_lora_kernel") if k in ktimes)
     gemm_kernel_ms = kavg(gemm_name)
     gemm_tflops = gemm_f / (gemm_kernel_ms * 1e-3) / 1e12
     gather_kernel_ms = kavg("gather_kernel")
@@ -1172,7 +1172,8 @@ def decode_main(args):
     attn_gbps = (kv_bytes + io_bytes) / (attn_ms * 1e-3) / 1e9
     # the projection of a few tokens: the weight-streaming GEMV (+ the LoRA
     # down-projection kernel); more tokens take the MFMA GEMM
-    proj = [k for k in ("gemv_kernel", "gemv_mfma_kernel", "lora_down_kernel", "gemm_lora_kernel", "gemm_kg2_kernel")
+    proj = [k for k in ("gemv_kernel", "gemv_mfma_kernel", "lora_down_kernel", "gemm_lora_kernel", "gemm_kg2_kernel",
+                        "gemm_ahead_kernel")
             if k in per_kernel]
     gemm_ms = sum(per_kernel[k]["avg_ms"] for k in proj)
     gemm_w_gbps = n_out * H * 2 / (gemm_ms * 1e-3) / 1e9
