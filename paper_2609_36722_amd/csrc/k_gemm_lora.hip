@@ -603,7 +603,7 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void gemm_ahead_kernel(const bf16_
                                                                     const bf16_t* __restrict__ b, int rank, int r_pad,
                                                                     int lora_cols, const float* __restrict__ t_part,
                                                                     int n_slice, GemmEpi epi, bf16_t* out, int n_mt,
-                                                                    int n_nt, int kt_split) {
+                                                                    int n_nt, int kt_split, int part_kt) {
   constexpr int NW = WN * WM;
   constexpr int TN = BN / WN, TM = BM / WM;
   constexpr int FN = TN / 32, FM = TM / 32;
@@ -657,9 +657,18 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void gemm_ahead_kernel(const bf16_
   // 44.7-46.5 us in step, 35.4 staggered; no change at 2560 and 9728).  Larger
   // token tiles share operand panels in L2 and lose by it (256 x 192 at 6000
   // tokens x 4096 -> 6144: 263-274 in step, 268-301 staggered).
-  const int kt_first = BM == 32 ? lin % n_kt : 0;
+  // Where the result itself is fp32 (part_kt > 0: logits) the order of the sum
+  // shows, so every workgroup takes k in order there (equal rows of W then give
+  // equal bits), and as at most eight parts of part_kt k-tiles that are summed
+  // apart and then pairwise: the largest logit of 16 x 4096 -> 151936 is off by
+  // 5.5e-8 relative (one chain over k: 3.5e-7; the matrix-core GEMV: 7.0e-8).
+  // 16 rows x 2560 -> 151936 with its argmax takes 153.5 us either way, 16 x
+  // 512 -> 40960 18.6 against 17.5; a staggered start gave the logits nothing.
+  constexpr bool kFew = BM == 32;
+  static_assert(!kFew || FN * FM == 1, "one accumulator block per wave");
+  const int kt_first = kFew && part_kt == 0 ? lin % n_kt : 0;
   auto copy = [&](int j, int kt, int slot) __attribute__((always_inline)) {
-    if (BM == 32) {
+    if (kFew) {
       kt += kt_first;
       kt -= kt >= n_kt ? n_kt : 0;
     }
@@ -729,8 +738,25 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void gemm_ahead_kernel(const bf16_
     slot = next;
     ++kt;
   };
-  while (kt + NST < n_kt) tile(with_copy);
-  while (kt < n_kt) tile(no_copy);
+  if (kFew && part_kt > 0) {
+    f32x16 part[4] = {f32x16{}, f32x16{}, f32x16{}, f32x16{}};  // part v goes to part[v % 4]
+#pragma unroll 1
+    while (kt < n_kt) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int end = min(kt + part_kt, n_kt);
+        acc[0][0] = f32x16{};
+        while (kt < end && kt + NST < n_kt) tile(with_copy);
+        while (kt < end) tile(no_copy);
+        part[i] += acc[0][0];
+        if (kt >= n_kt) break;
+      }
+    }
+    acc[0][0] = (part[0] + part[2]) + (part[1] + part[3]);
+  } else {
+    while (kt + NST < n_kt) tile(with_copy);
+    while (kt < n_kt) tile(no_copy);
+  }
 
   if (kt_split > 0) epi.out_f32 += (int64_t)split * M * N;
   lora_epilogue_store<FN, FM>(acc, n0 + wn * TN, m0 + wm * TM, wm * TM, l32, hi, M, N, b, rank, r_pad, lora_cols,
@@ -868,7 +894,7 @@ constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
 hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, const uint16_t* w, int n_tok, int n_out,
                        int hidden, const uint16_t* a, float scale, const uint16_t* b, int rank, int r_pad,
-                       int lora_cols, const float* t_part, int n_slice, GemmEpi epi, uint16_t* out,
+                       int lora_cols, const float* t_part, int n_slice, GemmEpi epi, uint16_t* out, int part_kt,
                        hipStream_t stream) {
 #define ATTUNER_GEMM(BM_, BN_, WN_, WM_, NST_)                                                                 \
   ATTUNER_LAUNCH("gemm_lora_kernel", (gemm_lora_kernel<BM_, BN_, WN_, WM_, NST_>), dim3((unsigned)grid),       \
@@ -881,7 +907,7 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 #define ATTUNER_GEMM_AHEAD(BM_, BN_, WN_, WM_, NST_)                                                            \
   ATTUNER_LAUNCH("gemm_ahead_kernel", (gemm_ahead_kernel<BM_, BN_, WN_, WM_, NST_>), dim3((unsigned)grid),    \
                  dim3(64 * (WN_) * (WM_)), stream, x, w, n_tok, n_out, hidden, b, rank, r_pad, lora_cols,       \
-                 t_part, n_slice, epi, out, (n_tok + (BM_) - 1) / (BM_), n_out / (BN_), kt_split)
+                 t_part, n_slice, epi, out, (n_tok + (BM_) - 1) / (BM_), n_out / (BN_), kt_split, part_kt)
   switch (tile) {
     case 0: ATTUNER_GEMM_AHEAD(256, 256, 2, 4, 2); break;
     case 1: ATTUNER_GEMM_AHEAD(256, 192, 2, 4, 2); break;
@@ -991,13 +1017,17 @@ hipError_t launch_gemm_any(const uint16_t* x, const uint16_t* w, int n_tok, int 
   const int n_slice = lora_down_slices(hidden, n_tok);
   if ((r_pad > 0 && t_part == nullptr && !kTiles[pl.tile].fuses)) return hipErrorInvalidValue;
   const int tiles = ((n_tok + kTiles[pl.tile].bm - 1) / kTiles[pl.tile].bm) * (n_out / kTiles[pl.tile].bn);
+  // an fp32 result (not a split's partial) of the few-token tiles: the GEMV's
+  // eight chains where that is what it would take, else no chain under 8 k-tiles
+  const int n_kt = pl.n_split > 1 ? pl.kt_split : hidden / BK;
+  const int part_kt = epi.mode == kEpiF32 ? std::max(n_tok <= kGemvMaxTok ? 1 : 8, (n_kt + 7) / 8) : 0;
   if (pl.n_split <= 1)
     return launch_tile(pl.tile, 0, tiles, x, w, n_tok, n_out, hidden, a, scale, b, rank, r_pad, lora_cols, t_part,
-                       n_slice, epi, out, stream);
+                       n_slice, epi, out, part_kt, stream);
   if (split_ws == nullptr || r_pad > 0) return hipErrorInvalidValue;
   const GemmEpi part{kEpiF32, nullptr, split_ws};
   hipError_t e = launch_tile(pl.tile, pl.kt_split, tiles * pl.n_split, x, w, n_tok, n_out, hidden, nullptr, 0.f,
-                             nullptr, 0, 0, 0, nullptr, n_slice, part, nullptr, stream);
+                             nullptr, 0, 0, 0, nullptr, n_slice, part, nullptr, part_kt, stream);
   if (e != hipSuccess) return e;
   const int64_t quads = (int64_t)n_tok * n_out / 4;
   ATTUNER_LAUNCH("splitk_reduce_kernel", splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), stream,

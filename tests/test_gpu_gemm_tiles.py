@@ -87,3 +87,55 @@ def test_few_tokens_capture_without_a_workspace():
             torch.cuda.synchronize()
             ref = x.double() @ w.double().t()
             assert_intermediate_close(out.double().cpu().numpy(), ref.cpu().numpy(), "linear")
+
+
+def _picked(n, H, V, seed):
+    """Rows x and a vocabulary whose rows i and j are both the copy of x[r] that
+    wins row r (logit sqrt(H) = 22 or more against unit normals)."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x, w = _normal(g, n, H), _normal(g, V, H, std=1 / math.sqrt(H))
+    at = torch.randperm(V, generator=g, device="cuda")[:2 * n].view(2, n)
+    w[at] = (x.float() / math.sqrt(H)).to(torch.bfloat16)
+    return x, w, at
+
+
+@pytest.mark.parametrize("n,H,V", [
+    (9, 2560, 8192), (16, 512, 40960), (12, 4096, 6144),     # past the GEMV: 20M weights and more
+    (17, 512, 4096), (32, 2560, 16384), (24, 1088, 19200),   # in key splits; unsplit; k-tiles no multiple of eight
+    (17, 64, 640), (20, 192, 1280),                          # one and three k-tiles
+    (8, 2560, 4096), (33, 2560, 16384),                      # either side: the GEMV and the larger tiles
+])
+def test_lm_head_equal_rows_tie(n, H, V):
+    # equal vocabulary rows give the same fp32 logit wherever they stand, so
+    # the smaller index wins
+    print(f"[case] lm_head tie n={n} H={H} V={V}", flush=True)
+    x, w, at = _picked(n, H, V, n + H + V)
+    ids = torch.empty(n, dtype=torch.int32, device="cuda")
+    with Context(ModelCfg(n_layers=1, hidden=H), pool_pages=0) as ctx:
+        ctx.lm_head_argmax(x, w, ids)
+        torch.cuda.synchronize()
+    assert ids.tolist() == at.min(0).values.tolist()
+
+
+@pytest.mark.parametrize("n,H,V", [(9, 4096, 6144), (16, 4096, 6144), (32, 4096, 6144), (16, 2560, 8192)])
+def test_lm_head_logit_precision(n, H, V):
+    # The winning logit's products have one sign, so a partial sum of j of m
+    # terms is j / m of it and each fp32 addition of the sum adds a rounding of
+    # 2^-24 / sqrt(3) of the partial sum (rms).  Eight parts of H / 128 matrix
+    # steps, summed pairwise: sqrt(1 + 2/4 + 4/16 + (H / 128) / 24) roundings,
+    # 1.75 at 4096; the bar is twice that.  One chain of H / 16 steps:
+    # sqrt(H / 48), 9.2 at 4096.
+    print(f"[case] lm_head precision n={n} H={H} V={V}", flush=True)
+    err = []
+    with Context(ModelCfg(n_layers=1, hidden=H), pool_pages=0) as ctx:
+        for seed in range(4):
+            x, w, at = _picked(n, H, V, 1000 * seed + n + H)
+            ids = torch.empty(n, dtype=torch.int32, device="cuda")
+            top = torch.empty(n, dtype=torch.float32, device="cuda")
+            ctx.lm_head_argmax(x, w, ids, top)
+            torch.cuda.synchronize()
+            ref = (x.double() * w[at[0]].double()).sum(-1)
+            err.append((top.double() / ref - 1).cpu())
+    rms = torch.cat(err).square().mean().sqrt().item()
+    bar = 2 * math.sqrt(1.75 + H / 128 / 24) * 2.0 ** -24 / math.sqrt(3)
+    assert rms <= bar, f"rms relative error {rms:.2e} > {bar:.2e}"
