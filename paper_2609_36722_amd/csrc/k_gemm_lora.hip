@@ -886,10 +886,9 @@ struct Tile {
   double kt_us, wg_us;
 };
 constexpr Tile kTiles[] = {{256, 256, false, 0, 1.57, 7}, {256, 192, false, 0, 1.24, 5}, {128, 256, false, 0, 0.88, 4},
-                           {128, 128, false, 0, 0.56, 3}, {128, 64, false, 0, 0.30, 2},  {256, 96, true, 52e9, 0, 0},
-                           {128, 128, true, 52e9, 0, 0},  {128, 96, true, 52e9, 0, 0},   {64, 96, true, 52e9, 0, 0},
-                           {64, 64, true, 52e9, 0, 0},    {128, 192, true, 60e9, 0, 0},  {128, 96, true, 60e9, 0, 0},
-                           {32, 128, false, 0, 0.22, 2},  {32, 64, false, 0, 0.20, 2}};
+                           {128, 128, false, 0, 0.56, 3}, {128, 64, false, 0, 0.30, 2},  {128, 128, true, 52e9, 0, 0},
+                           {64, 96, true, 52e9, 0, 0},    {64, 64, true, 52e9, 0, 0},    {128, 192, true, 60e9, 0, 0},
+                           {128, 96, true, 60e9, 0, 0},   {32, 128, false, 0, 0.22, 2},  {32, 64, false, 0, 0.20, 2}};
 constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
 hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, const uint16_t* w, int n_tok, int n_out,
@@ -914,15 +913,13 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
     case 2: ATTUNER_GEMM_AHEAD(128, 256, 4, 2, 3); break;
     case 3: ATTUNER_GEMM_AHEAD(128, 128, 4, 2, 4); break;
     case 4: ATTUNER_GEMM_AHEAD(128, 64, 2, 2, 6); break;
-    case 5: ATTUNER_GEMM(256, 96, 3, 4, 3); break;
-    case 6: ATTUNER_GEMM(128, 128, 2, 2, 4); break;
-    case 7: ATTUNER_GEMM(128, 96, 3, 2, 4); break;
-    case 8: ATTUNER_GEMM(64, 96, 3, 2, 5); break;
-    case 9: ATTUNER_GEMM(64, 64, 2, 2, 6); break;
-    case 10: ATTUNER_GEMM_KG2(128, 192, 2, 2, 3); break;
-    case 11: ATTUNER_GEMM_KG2(128, 96, 1, 2, 4); break;
-    case 12: ATTUNER_GEMM_AHEAD(32, 128, 4, 1, 4); break;
-    case 13: ATTUNER_GEMM_AHEAD(32, 64, 2, 1, 8); break;
+    case 5: ATTUNER_GEMM(128, 128, 2, 2, 4); break;
+    case 6: ATTUNER_GEMM(64, 96, 3, 2, 5); break;
+    case 7: ATTUNER_GEMM(64, 64, 2, 2, 6); break;
+    case 8: ATTUNER_GEMM_KG2(128, 192, 2, 2, 3); break;
+    case 9: ATTUNER_GEMM_KG2(128, 96, 1, 2, 4); break;
+    case 10: ATTUNER_GEMM_AHEAD(32, 128, 4, 1, 4); break;
+    case 11: ATTUNER_GEMM_AHEAD(32, 64, 2, 1, 8); break;
     default: return hipErrorInvalidValue;  // callers keep n_out a multiple of 64: 64x64 always fits
   }
 #undef ATTUNER_GEMM
