@@ -1513,12 +1513,12 @@ static attuner_status check_gemm_args(int32_t n_tok, const void* x, int32_t k_di
 // split workspace when the plan splits the k range.
 static attuner_status run_gemm(attuner_ctx* c, int32_t n_tok, const void* x, int32_t k_dim, const void* w,
                                int32_t n_out, GemmEpi epi, void* out, hipStream_t s) {
-  GemmPlan plan = plan_gemm(n_tok, n_out, k_dim, 0, true);
+  GemmPlan plan = plan_gemm(n_tok, n_out, k_dim, 0, epi.mode, kMaySplit | kMayFewTok);
   // a split needs a workspace: where it would have to grow on a captured
   // stream, a product of few tokens runs unsplit
   if (n_tok <= 32 && plan.n_split > 1 && (size_t)plan.n_split * n_tok * n_out * sizeof(float) > c->ws_split.cap &&
       capturing(s))
-    plan = plan_gemm(n_tok, n_out, k_dim, 0, false);
+    plan = plan_gemm(n_tok, n_out, k_dim, 0, epi.mode, 0);
   float* ws = nullptr;
   if (plan.n_split > 1) {
     attuner_status st = grow(c, c->ws_split, (size_t)plan.n_split * n_tok * n_out * sizeof(float), s, "key-split product");

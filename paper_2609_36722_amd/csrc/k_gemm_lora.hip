@@ -32,6 +32,7 @@
 #include <type_traits>
 
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "kernels.h"
@@ -874,21 +875,21 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   *reinterpret_cast<u32x2*>(out + m * N + n) = pk;
 }
 
-// A tile's cost on a chip with every CU busy.  Tiles of the read-ahead kernel:
-// microseconds per 64-deep k-tile and per workgroup (first k-tiles, epilogue),
-// measured.  The others (rate > 0): the operand ingest per CU the model
-// assumes (measured; the two-k-group kernel overlaps its MFMAs with the copies
-// best).  fuses: the kernel can compute the low-rank t itself.
+// A tile's cost, in microseconds: kt per 64-deep k-tile with every CU busy,
+// first for the launch, the first k-tiles and the epilogue, round for each
+// further round of 256 workgroups, and idle, the share of a round's k-tiles
+// that it saves with the CUs empty (power and the shared L2s).  fuse: what the
+// low-rank t adds to a k-tile where the kernel computes it itself (0: it can
+// not).  Fitted together, see plan_gemm.
 struct Tile {
   int bm, bn;
-  bool fuses;
-  double rate;
-  double kt_us, wg_us;
+  double kt, first, round, idle, fuse;
 };
-constexpr Tile kTiles[] = {{256, 256, false, 0, 1.57, 7}, {256, 192, false, 0, 1.24, 5}, {128, 256, false, 0, 0.88, 4},
-                           {128, 128, false, 0, 0.56, 3}, {128, 64, false, 0, 0.30, 2},  {128, 128, true, 52e9, 0, 0},
-                           {64, 96, true, 52e9, 0, 0},    {64, 64, true, 52e9, 0, 0},    {128, 192, true, 60e9, 0, 0},
-                           {128, 96, true, 60e9, 0, 0},   {32, 128, false, 0, 0.22, 2},  {32, 64, false, 0, 0.20, 2}};
+constexpr Tile kTiles[] = {
+    {256, 256, 1.614, 9.3, 6.9, 0.38, 0},    {256, 192, 1.239, 9.2, 5.9, 0.39, 0},    {128, 256, 0.915, 7.2, 3.9, 0.34, 0},
+    {128, 128, 0.561, 5.8, 1.5, 0.25, 0},    {128, 64, 0.343, 6.9, 3.3, 0.28, 0},     {128, 128, 0.593, 6.6, 4.7, 0.15, 0.21},
+    {64, 96, 0.345, 5.4, 3.4, 0.29, 0.09},   {64, 64, 0.252, 5.6, 2.5, 0.25, 0.24},   {128, 192, 0.702, 7.7, 3.2, 0.37, 0.24},
+    {128, 96, 0.400, 7.8, 4.0, 0.40, 0.25},  {32, 128, 0.291, 6.6, 2.2, 0.35, 0},     {32, 64, 0.127, 7.7, 2.8, 0.25, 0}};
 constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
 hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, const uint16_t* w, int n_tok, int n_out,
@@ -930,69 +931,73 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 
 }  // namespace
 
-// Tile and key split of a product, by a model fitted to gfx950 runs.  One
-// workgroup per CU at a time, in rounds of 256, plus a fixed 4 us.  A workgroup
-// of a read-ahead tile costs its measured time per k-tile (plus wg_us); of the
-// other tiles, the larger of its operand ingest ((BM + BN) * k-range * 2 bytes
-// at the tile's rate) and its MFMA work (2 BM BN k-range at about 6 TFLOP/s).
-// With all 256 CUs on large read-ahead tiles the chip is power-limited (a
-// 256 x 256 workgroup of 64 k-tiles: 160k shader cycles always, 101 us at 1.58
-// GHz with 256 CUs busy, 86 us with 192, 76 us with 128, 68 us with 64 or
-// fewer), so a partly filled round of these costs down to 2/3 of a full one;
-// the small tiles wait on memory and gain nothing.  With may_split, and
-// when a tile's workgroups would leave CUs idle, the k range may be split
-// across workgroups: shorter k-loops, paid for by the fp32 partials (split * M
-// * N * 8 bytes written and read at about 6 TB/s) and a 3 us reduce launch.
-// With a low-rank term that a tile may fuse, one that does not pays 10 us for
-// the down-projection's launch; the small read-ahead tiles, whose few waves
-// would each sum t's partials for 64 tokens, are left out (one layer of 184
-// tokens x 2560 at rank 64: 59.0 us with 128 x 64, 56.7 with 64 x 96).  The plan minimises the model; ties go to the earlier tile and to no
-// split.  Measured, chosen plan against the plan of the tiles without
-// read-ahead (us): 6000 tokens x 4096 -> 6144 262 (256 x 192) / 325; 1024 x
-// 4096 -> 24576 184 (256 x 192) / 205-225; 1024 x 12288 -> 4096 106 (128 x 256
-// in 2 splits) / 125; 1024 x 4096 -> 4096 42 (128 x 128) / 49; 256 x 9728 ->
-// 2560 24.7 (128 x 64 in 3) / 28.1; 256 x 4096 -> 2560 15.4 (128 x 64 in 3) /
-// 19.8.  The two-k-group tiles stay ahead at 6144 outputs of 512 (128 x 96,
-// 29.9 against 32.8) and 1024 tokens (128 x 192, 50.7 against 53.7).
-GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, bool may_split) {
-  constexpr double kMfmaPerCu = 6e12, kFixed = 4e-6;
-  constexpr double kPartBw = 6e12, kReduceLaunch = 3e-6, kLoraDown = 10e-6;
+// Tile and key split of a product: the least of a cost model over the tiles
+// and splits.  One workgroup per CU at a time, in rounds of 256; the k-tiles'
+// time and that of reading W from memory (8.54 TB/s, less with few workgroups)
+// are added as squares.
+// With kMaySplit, and when a tile's workgroups would leave CUs idle, the k
+// range may be split across workgroups: shorter k-loops, paid for by the fp32
+// partials (split * M * N * 8 bytes written and read at 7.26 TB/s) and the
+// reduce launch.  A low-rank term that the tile does not compute itself costs
+// the down-projection's launch and, per 16 ranks, the epilogue of each round.
+// With one the small read-ahead tiles are left out: their few waves would each
+// sum t's partials for 64 tokens (one layer of 184 tokens x 2560 at rank 64:
+// 59.0 us with 128 x 64, 56.7 with 64 x 96).  An fp32 result of up to
+// kGemvMaxTok tokens takes the tiles that sum it in parts, as exact as the GEMV
+// would.  Ties go to the earlier tile and to no split.
+//
+// All tiles are on one scale: the constants are fitted together to every tile
+// and split of 1,676 shapes (the model's products and generic ones, 9 to 9,000
+// tokens, ranks 0 to 64; weights read from memory), for the plan they choose to
+// be as near the fastest as the form allows: within 1 % of it in nine shapes of
+// ten.  Two scales, one of them an ingest rate without a cost per workgroup,
+// had put tiles first that were not (us, the plan of the two scales / now):
+// 5120 x 2560 -> 6144 at rank 16 193 (two-k-group 128 x 192) / 161 (256 x 256),
+// 8192 tokens at rank 32 320 / 259, 6144 x 4096 at rank 16 353 / 286 (256 x
+// 192); 512 x 12288 -> 4096 80 (128 x 64) / 64 (128 x 256 in 4 splits); 129 x
+// 2560 -> 2560 17.3 (128 x 128 in 6) / 13.0 (64 x 64 in 2); 1152 x 2560 -> 2560
+// 30.1 (128 x 128) / 25.8 (its read-ahead form).
+//
+// Up to kGemvDotMaxTok tokens, and without a split or below kGemvMaxWeights up
+// to kGemvMaxTok, the GEMV streams W (tile -1): 9 to 16 tokens x 4096 -> 4096
+// (16.8M weights) 11.2-12.5 us against 12.4-12.6 with 32-token tiles, 9 x 2560
+// -> 8192 (21M) 17.3 / 18.4, 9 to 16 x 9728 -> 2560 (24.9M) 18.3-21.5 /
+// 15.9-16.3.
+GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, int mode, int may) {
   constexpr int kCUs = 256;
   constexpr int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
-  // time of a round with n of the 256 CUs busy, in rounds with all busy
-  const auto round_of = [](const Tile& tl, int64_t n) {
-    return tl.rate == 0 && tl.bm * tl.bn > 128 * 128 ? 1.0 - std::min(kCUs - n, (int64_t)192) / 576.0 : 1.0;
-  };
-  constexpr double kHbm = 5.5e12;
-  constexpr int64_t kGemvMaxWeights = 20000000;
+  constexpr double kReadW = 8.54e6, kPartials = 7.26e6;        // bytes per us
+  constexpr double kReduce = 0.46, kPerSplit = 0.27;           // us
+  constexpr double kDown = 12.17, kTBase = 0.98, kTArea = 3.34;  // us; per 16 ranks, and more for 256 x 256 outputs
+  constexpr double kReadWgs = 224;  // fewer workgroups have too few bytes in flight
+  constexpr int64_t kGemvMaxWeights = 24000000;
   const int n_kt = k_dim / BK;
   GemmPlan best{-1, 1, 0};
   if (n_tok <= kGemvDotMaxTok ||
-      (n_tok <= kGemvMaxTok && (!may_split || (int64_t)n_out * k_dim < kGemvMaxWeights)))
+      (n_tok <= kGemvMaxTok && (!(may & kMaySplit) || (int64_t)n_out * k_dim < kGemvMaxWeights)))
     return best;
+  const double read_w = (double)n_out * k_dim * 2 / kReadW;
   double best_t = 0.0;
   for (int i = 0; i < kNumTiles; ++i) {
     const Tile& tl = kTiles[i];
-    if (n_out % tl.bn != 0 || (tl.bm == 32) != (may_split && n_tok <= 32)) continue;
-    if (r_pad > 0 && !tl.fuses && tl.bm * tl.bn <= 128 * 128) continue;
+    if (n_out % tl.bn != 0 || (tl.bm == 32 && (r_pad > 0 || n_tok > 32 || !(may & kMayFewTok)))) continue;
+    if (tl.bm != 32 && mode == kEpiF32 && n_tok <= kGemvMaxTok) continue;
+    if (r_pad > 0 && tl.fuse == 0 && tl.bm * tl.bn <= 128 * 128) continue;
+    const bool fused = r_pad > 0 && r_pad <= kGemmFusedLoraMaxRank && tl.fuse > 0;
     const int64_t tiles = (int64_t)((n_tok + tl.bm - 1) / tl.bm) * (n_out / tl.bn);
     for (int s : kSplits) {
       // splits only add workgroups where the tiles alone leave CUs idle
-      if (s > 1 && (!may_split || n_kt < 4 * s || tiles >= kCUs)) break;
+      if (s > 1 && (!(may & kMaySplit) || n_kt < 4 * s || tiles >= kCUs)) break;
       const int kts = (n_kt + s - 1) / s;
       const int used = (n_kt + kts - 1) / kts;  // splits that hold k-tiles
       // fp32 partials of every split: bounded, so that a reserved workspace holds any plan
       if (used > 1 && (int64_t)used * n_tok * n_out * 4 > kGemmSplitWsMaxBytes) break;
       const int64_t wgs = tiles * used, rest = wgs % kCUs;
-      const double k_range = (double)kts * BK;
-      const double k_time = tl.rate > 0 ? std::max((tl.bm + tl.bn) * k_range * 2 / tl.rate,
-                                                   2.0 * tl.bm * tl.bn * k_range / kMfmaPerCu)
-                                        : kts * tl.kt_us * 1e-6;
-      double t = k_time * ((double)(wgs / kCUs) + (rest > 0 ? round_of(tl, rest) : 0.0));
-      if (tl.bm == 32) t = std::max(t, (double)n_out * k_dim * 2 / (kHbm * std::min(1.0, wgs / (tl.bn == 64 ? 224.0 : 144.0))));
-      t += kFixed + (double)((wgs + kCUs - 1) / kCUs) * tl.wg_us * 1e-6;
-      if (r_pad > 0 && r_pad <= kGemmFusedLoraMaxRank && !tl.fuses) t += kLoraDown;
-      if (used > 1) t += (double)used * n_tok * n_out * 8 / kPartBw + kReduceLaunch;
+      const double rounds = (double)(wgs / kCUs) + (rest > 0 ? 1.0 - tl.idle * (double)(kCUs - rest) / kCUs : 0.0);
+      const double k_time = kts * tl.kt * (fused ? 1.0 + tl.fuse : 1.0) * rounds;
+      double t = std::sqrt(k_time * k_time + read_w * read_w / std::min(1.0, wgs / kReadWgs)) + tl.first + (double)((wgs - 1) / kCUs) * tl.round;
+      if (used > 1) t += kReduce + kPerSplit * used + (double)used * n_tok * n_out * 8 / kPartials;
+      if (r_pad > 0 && !fused) t += kDown + rounds * (kTBase + kTArea * tl.bm * tl.bn / 65536) * r_pad / 16;
       if (best.tile < 0 || t < best_t * (1.0 - 1e-9)) {
         best = GemmPlan{i, used, used > 1 ? kts : 0};
         best_t = t;
@@ -1012,7 +1017,7 @@ hipError_t launch_gemm_any(const uint16_t* x, const uint16_t* w, int n_tok, int 
   if (pl.tile < 0)
     return launch_gemv(x, w, n_tok, n_out, hidden, b, rank, r_pad, lora_cols, t_part, epi, out, stream);
   const int n_slice = lora_down_slices(hidden, n_tok);
-  if ((r_pad > 0 && t_part == nullptr && !kTiles[pl.tile].fuses)) return hipErrorInvalidValue;
+  if ((r_pad > 0 && t_part == nullptr && kTiles[pl.tile].fuse == 0)) return hipErrorInvalidValue;
   const int tiles = ((n_tok + kTiles[pl.tile].bm - 1) / kTiles[pl.tile].bm) * (n_out / kTiles[pl.tile].bn);
   // an fp32 result (not a split's partial) of the few-token tiles: the GEMV's
   // eight chains where that is what it would take, else no chain under 8 k-tiles
@@ -1038,7 +1043,7 @@ namespace {
 
 // No key split here: the caller has no workspace for it.
 GemmPlan plan_lora(int n_tok, int n_out, int hidden, int r_pad) {
-  return plan_gemm(n_tok, n_out, hidden, r_pad, false);
+  return plan_gemm(n_tok, n_out, hidden, r_pad, kEpiBf16, 0);
 }
 
 }  // namespace
@@ -1050,7 +1055,7 @@ GemmPlan plan_lora(int n_tok, int n_out, int hidden, int r_pad) {
 // smaller tiles hide it (1024 tokens, rank 32: 63.6 us fused, 67.4 separate).
 bool gemm_fuses_lora(int n_tok, int n_out, int hidden, int r_pad) {
   const GemmPlan pl = plan_lora(n_tok, n_out, hidden, r_pad);
-  return r_pad <= kGemmFusedLoraMaxRank && (pl.tile < 0 || kTiles[pl.tile].fuses);
+  return r_pad <= kGemmFusedLoraMaxRank && (pl.tile < 0 || kTiles[pl.tile].fuse > 0);
 }
 
 hipError_t launch_gemm_lora(const uint16_t* x, const uint16_t* w, int n_tok, int n_out, int hidden,

@@ -97,13 +97,17 @@ struct GemmEpi {
 // n_split > 1 splits the k range into chunks of kt_split 64-wide k-tiles and
 // needs a workspace of n_split * n_tok * n_out floats (never with a low-rank
 // term).  plan_gemm picks both by a cost model for a low-rank term of padded
-// rank r_pad (0: none); may_split: the caller has the workspace.
+// rank r_pad (0: none), an epilogue mode, and what the caller allows (GemmMay).
+enum GemmMay : int {
+  kMaySplit = 1,   // key splits: the caller has the workspace
+  kMayFewTok = 2,  // the 32-token tiles
+};
 struct GemmPlan {
   int tile;
   int n_split;
   int kt_split;
 };
-GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, bool may_split);
+GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, int mode, int may);
 hipError_t launch_gemm(const uint16_t* x, const uint16_t* w, int n_tok, int n_out, int k_dim, GemmEpi epi,
                        uint16_t* out, const GemmPlan& plan, float* split_ws, hipStream_t stream);
 

@@ -1,0 +1,87 @@
+"""The tile plan of the GEMM (plan_gemm, a host function): what it picks where
+several tiles were timed, and that every plan is one the launcher can run."""
+
+import ctypes as C
+import random
+
+import pytest
+
+from paper_2609_36722_amd import _lib
+
+
+class Plan(C.Structure):
+    _fields_ = [("tile", C.c_int), ("n_split", C.c_int), ("kt_split", C.c_int)]
+
+
+BF16, F32 = 0, 3             # epilogue modes
+SPLIT, FEW = 1, 2            # what a caller allows: key splits, the 32-token tiles
+
+
+def plan_gemm(n_tok, n_out, k_dim, r_pad, may, mode=BF16):
+    fn = getattr(_lib.lib(), "_ZN7attuner9plan_gemmEiiiiii")
+    fn.restype, fn.argtypes = Plan, [C.c_int] * 6
+    p = fn(n_tok, n_out, k_dim, r_pad, mode, may)
+    return p.tile, p.n_split, p.kt_split
+
+
+# the launcher's tiles (tokens, features); a: read-ahead, k: two k-groups
+TILES = ["256x256a", "256x192a", "128x256a", "128x128a", "128x64a", "128x128", "64x96", "64x64", "128x192k", "128x96k",
+         "32x128a", "32x64a"]
+SPLIT_WS_MAX, MAX_SPLIT = 64 << 20, 16
+
+
+def _dims(tile):
+    return tuple(int(v) for v in TILES[tile].rstrip("ak").split("x"))
+
+
+# (tokens, k, outputs, rank, a plain product): measured us of the plans near
+# the fastest and of one that another cost model had chosen, all timed in turn
+# on one gfx950 with weights read from memory
+@pytest.mark.parametrize("T,K,N,rank,plain,us", [
+    (32, 2560, 2560, 0, True, {"32x64a/4": 10.3, "64x64/4": 10.3, "32x128a/4": 10.6, "32x64a/6": 11.2}),
+    (17, 9728, 2560, 0, True, {"64x64/6": 16.2, "32x64a/6": 16.9}),
+    (65, 2560, 2560, 0, True, {"64x64/3": 11.4, "128x128/8": 15.2}),
+    (129, 2560, 2560, 0, True, {"64x64/2": 13.0, "128x128/6": 17.3}),
+    (80, 4096, 2560, 0, True, {"64x64/3": 13.8, "128x64a/4": 14.4, "128x128/11": 17.2}),
+    (160, 4096, 2560, 0, True, {"64x64/2": 15.5, "128x64a/3": 16.1, "128x128/6": 18.2}),
+    (448, 4096, 2560, 0, True, {"128x128a/3": 22.5, "128x64a/1": 25.2}),
+    (768, 9728, 2560, 0, True, {"128x256a/4": 54.3, "128x128a/2": 56.8, "128x64a/1": 65.8}),
+    (256, 12288, 4096, 0, True, {"128x128a/4": 42.0, "128x256a/8": 43.0, "128x64a/2": 49.7}),
+    (512, 12288, 4096, 0, True, {"128x256a/4": 63.7, "128x64a/1": 80.1}),
+    (1152, 2560, 2560, 0, True, {"128x128a/1": 25.8, "128x128/1": 30.1}),
+    (65, 4096, 24576, 0, True, {"128x96k/1": 44.4, "128x128a/1": 46.1, "128x192k/2": 49.0}),
+    (7168, 2560, 6144, 0, False, {"256x256a/1": 206.9, "256x192a/1": 214.9, "128x192k/1": 233.7}),
+    (5120, 2560, 6144, 16, False, {"256x256a/1": 160.6, "128x192k/1": 192.6}),
+    (8192, 2560, 6144, 32, False, {"256x256a/1": 259.0, "256x192a/1": 274.4, "128x192k/1": 319.6}),
+    (5120, 4096, 6144, 16, False, {"256x256a/1": 238.1, "128x192k/1": 287.7}),
+    (6144, 4096, 6144, 16, False, {"256x192a/1": 286.2, "128x192k/1": 353.5}),
+])
+def test_plan_is_near_the_fastest_measured(T, K, N, rank, plain, us):
+    tile, n_split, _ = plan_gemm(T, N, K, (rank + 15) // 16 * 16, SPLIT | FEW if plain else 0)
+    name = f"{TILES[tile]}/{n_split}"
+    assert name in us and us[name] <= 1.04 * min(us.values()), (name, us)
+
+
+def test_every_plan_can_be_launched():
+    rng = random.Random(36722)
+    for _ in range(50000):
+        T, K, N = int(2 ** rng.uniform(0, 13.5)), 64 * int(2 ** rng.uniform(0, 7.6)), 64 * int(2 ** rng.uniform(0, 9))
+        rank = rng.choice([0, 0, 0, 8, 16, 32, 33, 64])
+        r_pad = (rank + 15) // 16 * 16
+        may = 0 if rank else rng.choice([0, SPLIT, FEW, SPLIT | FEW])
+        mode = BF16 if rank else rng.choice([BF16, F32])
+        tile, n_split, kt_split = plan_gemm(T, N, K, r_pad, may, mode)
+        case = (T, K, N, rank, may, mode, tile, n_split, kt_split)
+        if tile < 0:  # the GEMV
+            assert T <= 16 and n_split == 1, case
+            continue
+        bm, bn = _dims(tile)
+        assert N % bn == 0, case
+        assert bm != 32 or (may & FEW and T <= 32), case   # these sum no low-rank term
+        assert bm == 32 or mode != F32 or T > 16, case     # logits in place of the GEMV's: summed in parts
+        if n_split == 1:
+            assert kt_split == 0, case
+            continue
+        n_kt = K // 64
+        assert may & SPLIT and n_split <= MAX_SPLIT and (n_split - 1) * kt_split < n_kt <= n_split * kt_split, case
+        assert n_split * T * N * 4 <= SPLIT_WS_MAX, case
