@@ -41,6 +41,14 @@
  *     (attuner_store_artifact(_host), attuner_assemble_*, attuner_embed,
  *     attuner_rms_norm with a row list) fails with EINVAL; nothing is
  *     enqueued then.  Every other call, within reserved limits, captures.
+ *     The key-split partials of a product (attuner_linear,
+ *     attuner_gate_up_swiglu, attuner_lm_head_argmax) and the LoRA slice
+ *     partials of attuner_qproj_lora / attuner_full_prefill for ranks up to 32
+ *     and more than 16 tokens are not among the workspaces that fail: where
+ *     they are too small during capture, the product runs in a form without
+ *     them.  That form sums in another order, so its results can differ from
+ *     the eager call's in the last bits and it can be slower; within reserved
+ *     limits both are the same.
  *   - Every call returns a status; on failure nothing is enqueued, and
  *     attuner_last_error() describes the cause.  Arguments are validated on
  *     the host before any launch.

@@ -839,18 +839,28 @@ attuner_status qproj_impl(attuner_ctx* c, int32_t n_tok, const void* x, const vo
   // ranks up to kGemmFusedLoraMaxRank: the GEMM computes t = scale * x A^T
   // itself where its tile hides the work; larger ranks, the GEMV of a few
   // tokens and the read-ahead tiles take a separate down-projection kernel first
+  GemmPlan plan = plan_gemm(n_tok, n_out, hidden, r_pad, kEpiBf16, kMayDown);
   float* t_part = nullptr;
-  if (r_pad > 0 && (n_tok <= kGemvMaxTok || !gemm_fuses_lora(n_tok, n_out, hidden, r_pad))) {
+  if (r_pad > 0 && !gemm_fuses_lora(plan, r_pad)) {
     const size_t part_bytes = (size_t)lora_down_slices(hidden, n_tok) * n_tok * r_pad * sizeof(float);
-    attuner_status st = grow(c, c->ws_lora, part_bytes, stream, "LoRA down-projection");
-    if (st != ATTUNER_OK) return st;
-    t_part = static_cast<float*>(c->ws_lora.ptr);
-    HIP_TRY(launch_lora_down(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(a), n_tok, hidden, rank,
-                             r_pad, scale, t_part, stream));
+    // where the workspace would have to grow on a captured stream, a tile that
+    // computes t itself
+    GemmPlan fused{-1, 1, 0};
+    if (part_bytes > c->ws_lora.cap && capturing(stream))
+      fused = plan_gemm(n_tok, n_out, hidden, r_pad, kEpiBf16, 0);
+    if (gemm_fuses_lora(fused, r_pad)) {
+      plan = fused;
+    } else {
+      attuner_status st = grow(c, c->ws_lora, part_bytes, stream, "LoRA down-projection");
+      if (st != ATTUNER_OK) return st;
+      t_part = static_cast<float*>(c->ws_lora.ptr);
+      HIP_TRY(launch_lora_down(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(a), n_tok, hidden, rank,
+                               r_pad, scale, t_part, stream));
+    }
   }
   HIP_TRY(launch_gemm_lora(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), n_tok, n_out, hidden,
                            static_cast<const uint16_t*>(a), scale, static_cast<const uint16_t*>(b), rank, r_pad,
-                           lora_cols, t_part, static_cast<uint16_t*>(out), stream));
+                           lora_cols, t_part, static_cast<uint16_t*>(out), plan, stream));
   return ATTUNER_OK;
 }
 
@@ -1515,10 +1525,9 @@ static attuner_status run_gemm(attuner_ctx* c, int32_t n_tok, const void* x, int
                                int32_t n_out, GemmEpi epi, void* out, hipStream_t s) {
   GemmPlan plan = plan_gemm(n_tok, n_out, k_dim, 0, epi.mode, kMaySplit | kMayFewTok);
   // a split needs a workspace: where it would have to grow on a captured
-  // stream, a product of few tokens runs unsplit
-  if (n_tok <= 32 && plan.n_split > 1 && (size_t)plan.n_split * n_tok * n_out * sizeof(float) > c->ws_split.cap &&
-      capturing(s))
-    plan = plan_gemm(n_tok, n_out, k_dim, 0, epi.mode, 0);
+  // stream, the product runs unsplit
+  if (plan.n_split > 1 && (size_t)plan.n_split * n_tok * n_out * sizeof(float) > c->ws_split.cap && capturing(s))
+    plan = plan_gemm(n_tok, n_out, k_dim, 0, epi.mode, kMayFewTok);
   float* ws = nullptr;
   if (plan.n_split > 1) {
     attuner_status st = grow(c, c->ws_split, (size_t)plan.n_split * n_tok * n_out * sizeof(float), s, "key-split product");

@@ -982,7 +982,7 @@ GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, int mode, int may
     const Tile& tl = kTiles[i];
     if (n_out % tl.bn != 0 || (tl.bm == 32 && (r_pad > 0 || n_tok > 32 || !(may & kMayFewTok)))) continue;
     if (tl.bm != 32 && mode == kEpiF32 && n_tok <= kGemvMaxTok) continue;
-    if (r_pad > 0 && tl.fuse == 0 && tl.bm * tl.bn <= 128 * 128) continue;
+    if (r_pad > 0 && tl.fuse == 0 && (!(may & kMayDown) || tl.bm * tl.bn <= 128 * 128)) continue;
     const bool fused = r_pad > 0 && r_pad <= kGemmFusedLoraMaxRank && tl.fuse > 0;
     const int64_t tiles = (int64_t)((n_tok + tl.bm - 1) / tl.bm) * (n_out / tl.bn);
     for (int s : kSplits) {
@@ -1011,13 +1011,12 @@ namespace {
 
 hipError_t launch_gemm_any(const uint16_t* x, const uint16_t* w, int n_tok, int n_out, int hidden, const uint16_t* a,
                            float scale, const uint16_t* b, int rank, int r_pad, int lora_cols, const float* t_part,
-                           GemmEpi epi, uint16_t* out, const GemmPlan* plan, float* split_ws, hipStream_t stream) {
+                           GemmEpi epi, uint16_t* out, const GemmPlan& pl, float* split_ws, hipStream_t stream) {
   if (n_tok == 0) return hipSuccess;
-  const GemmPlan pl = *plan;
   if (pl.tile < 0)
     return launch_gemv(x, w, n_tok, n_out, hidden, b, rank, r_pad, lora_cols, t_part, epi, out, stream);
   const int n_slice = lora_down_slices(hidden, n_tok);
-  if ((r_pad > 0 && t_part == nullptr && kTiles[pl.tile].fuse == 0)) return hipErrorInvalidValue;
+  if (r_pad > 0 && t_part == nullptr && !gemm_fuses_lora(pl, r_pad)) return hipErrorInvalidValue;
   const int tiles = ((n_tok + kTiles[pl.tile].bm - 1) / kTiles[pl.tile].bm) * (n_out / kTiles[pl.tile].bn);
   // an fp32 result (not a split's partial) of the few-token tiles: the GEMV's
   // eight chains where that is what it would take, else no chain under 8 k-tiles
@@ -1039,36 +1038,25 @@ hipError_t launch_gemm_any(const uint16_t* x, const uint16_t* w, int n_tok, int 
 
 }  // namespace
 
-namespace {
-
-// No key split here: the caller has no workspace for it.
-GemmPlan plan_lora(int n_tok, int n_out, int hidden, int r_pad) {
-  return plan_gemm(n_tok, n_out, hidden, r_pad, kEpiBf16, 0);
-}
-
-}  // namespace
-
 // Tiles that keep their MFMAs busy would show the redundant down-projection
 // (every feature tile of the adapted columns computes t for its tokens) in
 // full: at 5368 tokens x 4096 -> 6144 (rank 16) a fusing 256 x 256 tile took
 // 268 us against 244 us for lora_down_kernel + the GEMM reading t.  The
 // smaller tiles hide it (1024 tokens, rank 32: 63.6 us fused, 67.4 separate).
-bool gemm_fuses_lora(int n_tok, int n_out, int hidden, int r_pad) {
-  const GemmPlan pl = plan_lora(n_tok, n_out, hidden, r_pad);
-  return r_pad <= kGemmFusedLoraMaxRank && (pl.tile < 0 || kTiles[pl.tile].fuse > 0);
+bool gemm_fuses_lora(const GemmPlan& plan, int r_pad) {
+  return plan.tile >= 0 && r_pad <= kGemmFusedLoraMaxRank && kTiles[plan.tile].fuse > 0;
 }
 
 hipError_t launch_gemm_lora(const uint16_t* x, const uint16_t* w, int n_tok, int n_out, int hidden,
                             const uint16_t* a, float scale, const uint16_t* b, int rank, int r_pad, int lora_cols,
-                            const float* t_part, uint16_t* out, hipStream_t stream) {
-  const GemmPlan pl = plan_lora(n_tok, n_out, hidden, r_pad);
+                            const float* t_part, uint16_t* out, const GemmPlan& plan, hipStream_t stream) {
   return launch_gemm_any(x, w, n_tok, n_out, hidden, a, scale, b, rank, r_pad, lora_cols, t_part,
-                         GemmEpi{kEpiBf16, nullptr, nullptr}, out, &pl, nullptr, stream);
+                         GemmEpi{kEpiBf16, nullptr, nullptr}, out, plan, nullptr, stream);
 }
 
 hipError_t launch_gemm(const uint16_t* x, const uint16_t* w, int n_tok, int n_out, int k_dim, GemmEpi epi,
                        uint16_t* out, const GemmPlan& plan, float* split_ws, hipStream_t stream) {
-  return launch_gemm_any(x, w, n_tok, n_out, k_dim, nullptr, 0.f, nullptr, 0, 0, 0, nullptr, epi, out, &plan,
+  return launch_gemm_any(x, w, n_tok, n_out, k_dim, nullptr, 0.f, nullptr, 0, 0, 0, nullptr, epi, out, plan,
                          split_ws, stream);
 }
 

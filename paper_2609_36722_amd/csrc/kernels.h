@@ -62,24 +62,8 @@ hipError_t launch_gather(const int32_t* table_dev, int64_t n_entries, const uint
 // dimension: t_part[lora_down_slices(hidden, n_tok)][n_tok][r_pad]; ranks
 // rank .. r_pad-1 are zero.  The slice count never exceeds that of one token.
 int lora_down_slices(int hidden, int n_tok);
-// Whether the projection GEMM of this shape and padded rank computes t itself
-// (rank <= kGemmFusedLoraMaxRank, and a tile that fuses it); otherwise
-// launch_lora_down runs first.
-bool gemm_fuses_lora(int n_tok, int n_out, int hidden, int r_pad);
 hipError_t launch_lora_down(const uint16_t* x, const uint16_t* a, int n_tok, int hidden, int rank, int r_pad,
                             float scale, float* t_part, hipStream_t stream);
-
-// out[i][n] = x[i] . w[n] + (n < lora_cols ? t[i] . b[n] : 0) (r_pad = 0: no
-// adapter).  t is the sum of the slices of t_part when t_part is given;
-// with t_part null (and r_pad <= kGemmFusedLoraMaxRank) the kernel computes
-// t = scale * x a^T itself, except for n_tok <= kGemvMaxTok, which needs
-// t_part.
-constexpr int kGemmFusedLoraMaxRank = 32;
-hipError_t launch_gemm_lora(const uint16_t* x, const uint16_t* w, int n_tok, int n_out, int hidden,
-                            const uint16_t* a, float scale, const uint16_t* b, int rank, int r_pad, int lora_cols,
-                            const float* t_part, uint16_t* out, hipStream_t stream);
-
-// ---- the decoder layer around the path: plain GEMMs with other epilogues --
 
 // What the GEMM stores for C = x W^T ([n_tok][n_out], fp32 accumulate):
 //   kEpiBf16      out = C (bf16)
@@ -93,14 +77,15 @@ struct GemmEpi {
   const uint16_t* residual;
   float* out_f32;
 };
-// Tile (index into the launcher's tile list) and key split of a product:
-// n_split > 1 splits the k range into chunks of kt_split 64-wide k-tiles and
-// needs a workspace of n_split * n_tok * n_out floats (never with a low-rank
-// term).  plan_gemm picks both by a cost model for a low-rank term of padded
-// rank r_pad (0: none), an epilogue mode, and what the caller allows (GemmMay).
+// Tile (index into the launcher's tile list; -1: the GEMV) and key split of a
+// product: n_split > 1 splits the k range into chunks of kt_split 64-wide
+// k-tiles and needs a workspace of n_split * n_tok * n_out floats (never with a
+// low-rank term).  plan_gemm picks both by a cost model for a low-rank term of
+// padded rank r_pad (0: none), an epilogue mode, and what the caller allows.
 enum GemmMay : int {
   kMaySplit = 1,   // key splits: the caller has the workspace
   kMayFewTok = 2,  // the 32-token tiles
+  kMayDown = 4,    // with r_pad > 0, tiles that do not compute t: the caller runs launch_lora_down
 };
 struct GemmPlan {
   int tile;
@@ -108,6 +93,20 @@ struct GemmPlan {
   int kt_split;
 };
 GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, int mode, int may);
+
+// out[i][n] = x[i] . w[n] + (n < lora_cols ? t[i] . b[n] : 0) (r_pad = 0: no
+// adapter).  t is the sum of the slices of t_part when t_part is given; with
+// t_part null the kernel computes t = scale * x a^T itself, which the plan must
+// be one for (gemm_fuses_lora: r_pad <= kGemmFusedLoraMaxRank and a tile that
+// fuses it; the GEMV does not).
+constexpr int kGemmFusedLoraMaxRank = 32;
+bool gemm_fuses_lora(const GemmPlan& plan, int r_pad);
+hipError_t launch_gemm_lora(const uint16_t* x, const uint16_t* w, int n_tok, int n_out, int hidden,
+                            const uint16_t* a, float scale, const uint16_t* b, int rank, int r_pad, int lora_cols,
+                            const float* t_part, uint16_t* out, const GemmPlan& plan, hipStream_t stream);
+
+// ---- the decoder layer around the path: plain GEMMs with other epilogues --
+
 hipError_t launch_gemm(const uint16_t* x, const uint16_t* w, int n_tok, int n_out, int k_dim, GemmEpi epi,
                        uint16_t* out, const GemmPlan& plan, float* split_ws, hipStream_t stream);
 

@@ -14,7 +14,7 @@ class Plan(C.Structure):
 
 
 BF16, F32 = 0, 3             # epilogue modes
-SPLIT, FEW = 1, 2            # what a caller allows: key splits, the 32-token tiles
+SPLIT, FEW, DOWN = 1, 2, 4   # what a caller allows: key splits, the 32-token tiles, t by a kernel of its own
 
 
 def plan_gemm(n_tok, n_out, k_dim, r_pad, may, mode=BF16):
@@ -27,6 +27,7 @@ def plan_gemm(n_tok, n_out, k_dim, r_pad, may, mode=BF16):
 # the launcher's tiles (tokens, features); a: read-ahead, k: two k-groups
 TILES = ["256x256a", "256x192a", "128x256a", "128x128a", "128x64a", "128x128", "64x96", "64x64", "128x192k", "128x96k",
          "32x128a", "32x64a"]
+FUSES = {"128x128", "64x96", "64x64", "128x192k", "128x96k"}   # compute a low-rank t of up to 32 ranks
 SPLIT_WS_MAX, MAX_SPLIT = 64 << 20, 16
 
 
@@ -57,7 +58,7 @@ def _dims(tile):
     (6144, 4096, 6144, 16, False, {"256x192a/1": 286.2, "128x192k/1": 353.5}),
 ])
 def test_plan_is_near_the_fastest_measured(T, K, N, rank, plain, us):
-    tile, n_split, _ = plan_gemm(T, N, K, (rank + 15) // 16 * 16, SPLIT | FEW if plain else 0)
+    tile, n_split, _ = plan_gemm(T, N, K, (rank + 15) // 16 * 16, SPLIT | FEW if plain else DOWN)
     name = f"{TILES[tile]}/{n_split}"
     assert name in us and us[name] <= 1.04 * min(us.values()), (name, us)
 
@@ -68,7 +69,7 @@ def test_every_plan_can_be_launched():
         T, K, N = int(2 ** rng.uniform(0, 13.5)), 64 * int(2 ** rng.uniform(0, 7.6)), 64 * int(2 ** rng.uniform(0, 9))
         rank = rng.choice([0, 0, 0, 8, 16, 32, 33, 64])
         r_pad = (rank + 15) // 16 * 16
-        may = 0 if rank else rng.choice([0, SPLIT, FEW, SPLIT | FEW])
+        may = rng.choice([DOWN, DOWN if rank > 32 else 0]) if rank else rng.choice([0, SPLIT, FEW, SPLIT | FEW])
         mode = BF16 if rank else rng.choice([BF16, F32])
         tile, n_split, kt_split = plan_gemm(T, N, K, r_pad, may, mode)
         case = (T, K, N, rank, may, mode, tile, n_split, kt_split)
@@ -78,6 +79,7 @@ def test_every_plan_can_be_launched():
         bm, bn = _dims(tile)
         assert N % bn == 0, case
         assert bm != 32 or (may & FEW and T <= 32), case   # these sum no low-rank term
+        assert not rank or may & DOWN or TILES[tile] in FUSES, case
         assert bm == 32 or mode != F32 or T > 16, case     # logits in place of the GEMV's: summed in parts
         if n_split == 1:
             assert kt_split == 0, case

@@ -89,6 +89,52 @@ def test_few_tokens_capture_without_a_workspace():
             assert_intermediate_close(out.double().cpu().numpy(), ref.cpu().numpy(), "linear")
 
 
+@pytest.mark.parametrize("call,T,K,N,rank", [
+    # key splits when eager; captured with nothing reserved they run unsplit
+    ("linear", 24, 12288, 4096, 0), ("linear", 65, 2560, 2560, 0), ("linear", 256, 4096, 4096, 0),
+    ("linear", 1100, 9728, 2560, 0), ("gate_up", 60, 2560, 19456, 0),
+    # t from the separate kernel when eager; captured, a tile that computes t
+    ("qproj", 1152, 2560, 6144, 16), ("qproj", 2500, 4096, 6144, 32),
+])
+def test_capture_with_nothing_reserved(call, T, K, N, rank):
+    print(f"[case] {call} captured, nothing reserved: T={T} K={K} N={N} rank={rank}", flush=True)
+    nq = 4096
+    g = torch.Generator(device="cuda").manual_seed(T + K + N)
+    w = _normal(g, N, K, std=1 / math.sqrt(K))
+    a = _normal(g, rank, K, std=1 / math.sqrt(K)) if rank else None
+    b = _normal(g, nq, rank) if rank else None
+    x = torch.zeros(T, K, dtype=torch.bfloat16, device="cuda")
+    out = torch.empty(T, N // 2 if call == "gate_up" else N, dtype=torch.bfloat16, device="cuda")
+
+    def run(ctx, o):
+        if call == "linear":
+            ctx.linear(x, w, o)
+        elif call == "gate_up":
+            ctx.gate_up_swiglu(x, w, o)
+        else:
+            ctx.qproj_lora(x, w, a, b, rank, 0.5, nq, o)
+
+    cfg = ModelCfg(n_layers=1, hidden=K if call == "qproj" else 256)
+    with Context(cfg, pool_pages=0) as ctx, Context(cfg, pool_pages=0) as eager:
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            run(ctx, out)
+        for _ in range(3):
+            x.copy_(_normal(g, T, K))
+            graph.replay()
+            plain = torch.empty_like(out)
+            run(eager, plain)
+            torch.cuda.synchronize()
+            ref = x.double() @ w.double().t()
+            if rank:
+                ref[:, :nq] += 0.5 * (x.double() @ a.double().t()) @ b.double().t()
+            if call == "gate_up":
+                ref = torch.nn.functional.silu(ref[:, 0::2]) * ref[:, 1::2]
+            for got, what in ((out, "captured"), (plain, "eager")):
+                assert_intermediate_close(got.double().cpu().numpy(), ref.cpu().numpy(), what)
+
+
 def _picked(n, H, V, seed):
     """Rows x and a vocabulary whose rows i and j are both the copy of x[r] that
     wins row r (logit sqrt(H) = 22 or more against unit normals)."""
