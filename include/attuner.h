@@ -124,7 +124,9 @@ typedef struct {
 /* Size every workspace and the RoPE table of the context for calls within
  * `limits`, so that such calls allocate nothing (what a caller needs before
  * capturing them into a HIP graph, see the conventions above).  Also frees
- * buffers that earlier growth replaced.  Synchronous: waits for the device.
+ * buffers that earlier growth replaced: a graph captured on this context
+ * before such growth must not be replayed after this call, it may hold their
+ * addresses.  Synchronous: waits for the device.
  * Errors: EINVAL (negative limit), ERANGE (max_rank > ATTUNER_MAX_RANK),
  * ENOMEM, EDEVICE. */
 attuner_status attuner_reserve(attuner_ctx* ctx, const attuner_limits* limits);

@@ -949,10 +949,11 @@ attuner_status attuner_reserve(attuner_ctx* c, const attuner_limits* lim) {
   if (st == ATTUNER_OK && T > 0)
     st = grow(c, c->ws_qkv, (size_t)T * (nq + 2 * nkv) * sizeof(uint16_t), s, "full-prefill projection");
   if (st == ATTUNER_OK && T > 0) st = grow(c, c->ws_rows, (size_t)T * sizeof(int32_t), s, "row list");
-  const int64_t widest = std::max(lim->max_out, lim->max_vocab);
-  if (st == ATTUNER_OK && T > 0 && widest > 0)
-    st = grow(c, c->ws_split,
-              (size_t)std::min<int64_t>(kGemmSplitWsMaxBytes, (int64_t)kMaxGemmSplit * std::max<int64_t>(T, lim->max_lm_rows) * widest * 4), s,
+  // fp32 partials of a product's key splits: of max_tokens rows, and of the LM
+  // head's rows on their own
+  const int64_t split_sums = std::max(T * std::max(lim->max_out, lim->max_vocab), (int64_t)lim->max_lm_rows * lim->max_vocab);
+  if (st == ATTUNER_OK && split_sums > 0)
+    st = grow(c, c->ws_split, (size_t)std::min<int64_t>(kGemmSplitWsMaxBytes, (int64_t)kMaxGemmSplit * split_sums * 4), s,
               "key-split product");
   if (st == ATTUNER_OK && lim->max_lm_rows > 0 && lim->max_vocab > 0)
     st = grow(c, c->ws_logits,

@@ -135,6 +135,25 @@ def test_capture_with_nothing_reserved(call, T, K, N, rank):
                 assert_intermediate_close(got.double().cpu().numpy(), ref.cpu().numpy(), what)
 
 
+@pytest.mark.parametrize("n,H,V", [(16, 8192, 8192), (128, 4096, 4096)])
+def test_reserved_lm_head_allocates_nothing(n, H, V):
+    # limits that name the LM head alone cover its key-split partials too (1 and
+    # 4 MiB here): the first call takes no device memory
+    print(f"[case] lm_head reserved by its own limits, n={n} H={H} V={V}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n + H + V)
+    x, w = _normal(g, n, H), _normal(g, V, H, std=1 / math.sqrt(H))
+    ids = torch.empty(n, dtype=torch.int32, device="cuda")
+    with Context(ModelCfg(n_layers=1, hidden=H), pool_pages=0) as ctx, \
+            Context(ModelCfg(n_layers=1, hidden=H), pool_pages=0) as other:
+        other.lm_head_argmax(x, w, ids)  # kernels loaded, another context's workspaces grown
+        ctx.reserve(max_lm_rows=n, max_vocab=V)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        ctx.lm_head_argmax(x, w, ids)
+        torch.cuda.synchronize()
+        assert torch.cuda.mem_get_info()[0] == before
+
+
 def _picked(n, H, V, seed):
     """Rows x and a vocabulary whose rows i and j are both the copy of x[r] that
     wins row r (logit sqrt(H) = 22 or more against unit normals)."""
