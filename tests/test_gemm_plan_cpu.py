@@ -1,33 +1,12 @@
 """The tile plan of the GEMM (plan_gemm, a host function): what it picks where
 several tiles were timed, and that every plan is one the launcher can run."""
 
-import ctypes as C
 import random
 
 import pytest
 
-from paper_2609_36722_amd import _lib
+from tests._plan import BF16, DOWN, F32, FEW, FUSES, SPLIT, TILES, plan_gemm
 
-
-class Plan(C.Structure):
-    _fields_ = [("tile", C.c_int), ("n_split", C.c_int), ("kt_split", C.c_int)]
-
-
-BF16, F32 = 0, 3             # epilogue modes
-SPLIT, FEW, DOWN = 1, 2, 4   # what a caller allows: key splits, the 32-token tiles, t by a kernel of its own
-
-
-def plan_gemm(n_tok, n_out, k_dim, r_pad, may, mode=BF16):
-    fn = getattr(_lib.lib(), "_ZN7attuner9plan_gemmEiiiiii")
-    fn.restype, fn.argtypes = Plan, [C.c_int] * 6
-    p = fn(n_tok, n_out, k_dim, r_pad, mode, may)
-    return p.tile, p.n_split, p.kt_split
-
-
-# the launcher's tiles (tokens, features); a: read-ahead, k: two k-groups
-TILES = ["256x256a", "256x192a", "128x256a", "128x128a", "128x64a", "128x128", "64x96", "64x64", "128x192k", "128x96k",
-         "32x128a", "32x64a"]
-FUSES = {"128x128", "64x96", "64x64", "128x192k", "128x96k"}   # compute a low-rank t of up to 32 ranks
 SPLIT_WS_MAX, MAX_SPLIT = 64 << 20, 16
 
 
