@@ -15,9 +15,9 @@
 // fragments read one k-step ahead; plain products and those whose low-rank t
 // a kernel of its own computes).  At suffix sizes the operand ingest per CU is the
 // ceiling (measured on gfx950: about 58 GB/s per CU, 15 TB/s out of the L2s,
-// the same rate hipBLASLt's kernels reach on these shapes), so the tile shape
-// is chosen to minimise ingested bytes, M N K 2 (1/BM + 1/BN), while keeping
-// every CU busy, and the copies are spread between the MFMAs so that the
+// the same rate hipBLASLt's kernels reach on these shapes): large tiles ingest
+// less, M N K 2 (1/BM + 1/BN) bytes, small ones keep every CU busy (plan_gemm
+// weighs them), and the copies are spread between the MFMAs so that the
 // compute hides under the ingest.  LDS rows are 128 bytes (eight 16-byte
 // chunks); chunk c of row r is stored at c ^ ((r >> 1) & 7), so the 16 rows
 // one operand read touches in a cycle land on 16 distinct bank groups.
