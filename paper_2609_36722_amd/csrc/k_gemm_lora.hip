@@ -886,10 +886,11 @@ struct Tile {
   double kt, first, round, idle, fuse;
 };
 constexpr Tile kTiles[] = {
-    {256, 256, 1.614, 9.3, 6.9, 0.38, 0},    {256, 192, 1.239, 9.2, 5.9, 0.39, 0},    {128, 256, 0.915, 7.2, 3.9, 0.34, 0},
-    {128, 128, 0.561, 5.8, 1.5, 0.25, 0},    {128, 64, 0.343, 6.9, 3.3, 0.28, 0},     {128, 128, 0.593, 6.6, 4.7, 0.15, 0.21},
-    {64, 96, 0.345, 5.4, 3.4, 0.29, 0.09},   {64, 64, 0.252, 5.6, 2.5, 0.25, 0.24},   {128, 192, 0.702, 7.7, 3.2, 0.37, 0.24},
-    {128, 96, 0.400, 7.8, 4.0, 0.40, 0.25},  {32, 128, 0.291, 6.6, 2.2, 0.35, 0},     {32, 64, 0.127, 7.7, 2.8, 0.25, 0}};
+    {256, 256, 1.615, 8.6, 7.6, 0.39, 0},    {256, 192, 1.239, 10.0, 5.7, 0.39, 0},   {128, 256, 0.923, 6.4, 3.9, 0.37, 0},
+    {128, 128, 0.559, 5.8, 1.8, 0.25, 0},    {128, 64, 0.351, 6.5, 4.0, 0.29, 0},     {128, 128, 0.592, 6.8, 4.4, 0.16, 0.21},
+    {64, 96, 0.340, 5.4, 3.1, 0.24, 0.09},   {64, 64, 0.253, 5.3, 2.5, 0.30, 0.30},   {128, 192, 0.703, 7.3, 3.3, 0.40, 0.24},
+    {128, 96, 0.394, 7.6, 4.7, 0.32, 0.26},  {32, 128, 0.360, 6.2, 0.6, 0.45, 0},     {32, 64, 0.256, 5.3, 2.1, 0.36, 0},
+    {128, 256, 0.908, 9.9, 4.0, 0.36, 0.20}};
 constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
 hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, const uint16_t* w, int n_tok, int n_out,
@@ -921,6 +922,7 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
     case 9: ATTUNER_GEMM_KG2(128, 96, 1, 2, 4); break;
     case 10: ATTUNER_GEMM_AHEAD(32, 128, 4, 1, 4); break;
     case 11: ATTUNER_GEMM_AHEAD(32, 64, 2, 1, 8); break;
+    case 12: ATTUNER_GEMM(128, 256, 4, 2, 3); break;
     default: return hipErrorInvalidValue;  // callers keep n_out a multiple of 64: 64x64 always fits
   }
 #undef ATTUNER_GEMM
@@ -933,11 +935,11 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 
 // Tile and key split of a product: the least of a cost model over the tiles
 // and splits.  One workgroup per CU at a time, in rounds of 256; the k-tiles'
-// time and that of reading W from memory (8.54 TB/s, less with few workgroups)
+// time and that of reading W from memory (8.08 TB/s, less with few workgroups)
 // are added as squares.
 // With kMaySplit, and when a tile's workgroups would leave CUs idle, the k
 // range may be split across workgroups: shorter k-loops, paid for by the fp32
-// partials (split * M * N * 8 bytes written and read at 7.26 TB/s) and the
+// partials (split * M * N * 8 bytes written and read at 7.44 TB/s) and the
 // reduce launch.  A low-rank term that the tile does not compute itself costs
 // the down-projection's launch and, per 16 ranks, the epilogue of each round.
 // With one the small read-ahead tiles are left out: their few waves would each
@@ -947,16 +949,20 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 // would.  Ties go to the earlier tile and to no split.
 //
 // All tiles are on one scale: the constants are fitted together to every tile
-// and split of 1,676 shapes (the model's products and generic ones, 9 to 9,000
+// and split of 2,600 shapes (the model's products and generic ones, 9 to 9,000
 // tokens, ranks 0 to 64; weights read from memory), for the plan they choose to
-// be as near the fastest as the form allows: within 1 % of it in nine shapes of
-// ten.  Two scales, one of them an ingest rate without a cost per workgroup,
-// had put tiles first that were not (us, the plan of the two scales / now):
+// be as near the fastest as the form allows: within 1 % of it in nine of ten of
+// the model's shapes, within 2 % of generic ones.  Two scales, one of them an
+// ingest rate without a cost per workgroup, had put tiles first that were not
+// (us, the plan of the two scales / now):
 // 5120 x 2560 -> 6144 at rank 16 193 (two-k-group 128 x 192) / 161 (256 x 256),
 // 8192 tokens at rank 32 320 / 259, 6144 x 4096 at rank 16 353 / 286 (256 x
 // 192); 512 x 12288 -> 4096 80 (128 x 64) / 64 (128 x 256 in 4 splits); 129 x
 // 2560 -> 2560 17.3 (128 x 128 in 6) / 13.0 (64 x 64 in 2); 1152 x 2560 -> 2560
-// 30.1 (128 x 128) / 25.8 (its read-ahead form).
+// 30.1 (128 x 128) / 25.8 (its read-ahead form).  128 x 256 has both forms: the
+// one that computes t saves the down-projection's launch where k is short or the
+// rounds are few (1152 x 2560 -> 6144 at rank 16 52.7, read-ahead 57.2; 410 x
+// 576 -> 10496 18.5 / 24.8), the read-ahead one is faster without a low-rank term.
 //
 // Up to kGemvDotMaxTok tokens, and without a split or below kGemvMaxWeights up
 // to kGemvMaxTok, the GEMV streams W (tile -1): 9 to 16 tokens x 4096 -> 4096
@@ -966,10 +972,10 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, int mode, int may) {
   constexpr int kCUs = 256;
   constexpr int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
-  constexpr double kReadW = 8.54e6, kPartials = 7.26e6;        // bytes per us
-  constexpr double kReduce = 0.46, kPerSplit = 0.27;           // us
-  constexpr double kDown = 12.17, kTBase = 0.98, kTArea = 3.34;  // us; per 16 ranks, and more for 256 x 256 outputs
-  constexpr double kReadWgs = 224;  // fewer workgroups have too few bytes in flight
+  constexpr double kReadW = 8.08e6, kPartials = 7.44e6;        // bytes per us
+  constexpr double kReduce = 0.54, kPerSplit = 0.26;           // us
+  constexpr double kDown = 10.74, kTBase = 1.10, kTArea = 3.03;  // us; per 16 ranks, and more for 256 x 256 outputs
+  constexpr double kReadWgs = 184;  // fewer workgroups have too few bytes in flight
   constexpr int64_t kGemvMaxWeights = 24000000;
   const int n_kt = k_dim / BK;
   GemmPlan best{-1, 1, 0};

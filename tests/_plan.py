@@ -10,8 +10,8 @@ SPLIT, FEW, DOWN = 1, 2, 4   # what a caller allows: key splits, the 32-token ti
 
 # the launcher's tiles (tokens x features); a: read-ahead, k: two k-groups
 TILES = ["256x256a", "256x192a", "128x256a", "128x128a", "128x64a", "128x128", "64x96", "64x64", "128x192k", "128x96k",
-         "32x128a", "32x64a"]
-FUSES = {"128x128", "64x96", "64x64", "128x192k", "128x96k"}   # compute a low-rank t of up to 32 ranks
+         "32x128a", "32x64a", "128x256"]
+FUSES = {"128x256", "128x128", "64x96", "64x64", "128x192k", "128x96k"}   # compute a low-rank t of up to 32 ranks
 KERNELS = {"a": "gemm_ahead_kernel", "k": "gemm_kg2_kernel"}
 
 

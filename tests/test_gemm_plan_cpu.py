@@ -34,6 +34,9 @@ def _dims(tile):
     (5120, 2560, 6144, 16, False, {"256x256a/1": 160.6, "128x192k/1": 192.6}),
     (8192, 2560, 6144, 32, False, {"256x256a/1": 259.0, "256x192a/1": 274.4, "128x192k/1": 319.6}),
     (5120, 4096, 6144, 16, False, {"256x256a/1": 238.1, "128x192k/1": 287.7}),
+    (1152, 2560, 6144, 16, False, {"128x256/1": 52.7, "128x256a/1": 57.2}),
+    (5384, 704, 4096, 16, False, {"128x256/1": 57.9, "128x256a/1": 62.6, "128x128/1": 74.8}),
+    (316, 256, 18432, 24, False, {"128x256/1": 14.3, "128x256a/1": 18.8, "128x128/1": 18.9}),
     (6144, 4096, 6144, 16, False, {"256x192a/1": 286.2, "128x192k/1": 353.5}),
 ])
 def test_plan_is_near_the_fastest_measured(T, K, N, rank, plain, us):
