@@ -964,11 +964,15 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 // rounds are few (1152 x 2560 -> 6144 at rank 16 52.7, read-ahead 57.2; 410 x
 // 576 -> 10496 18.5 / 24.8), the read-ahead one is faster without a low-rank term.
 //
-// Up to kGemvDotMaxTok tokens, and without a split or below kGemvMaxWeights up
-// to kGemvMaxTok, the GEMV streams W (tile -1): 9 to 16 tokens x 4096 -> 4096
-// (16.8M weights) 11.2-12.5 us against 12.4-12.6 with 32-token tiles, 9 x 2560
-// -> 8192 (21M) 17.3 / 18.4, 9 to 16 x 9728 -> 2560 (24.9M) 18.3-21.5 /
-// 15.9-16.3.
+// The GEMV streams W (tile -1) up to kGemvDotMaxTok tokens, up to kGemvMaxTok
+// without a split, and up to kGemvMaxTok where it costs less.  Its matrix-core
+// form has one workgroup of 16 rows on every CU up to 4096 outputs, and time
+// goes with their number and k (fitted, within 10 %); the dot-product form (k
+// no multiple of 128) reads x again for every row pair (within 7 %).  Measured, GEMV against
+// the best tile, us: 16 tokens x 4096 -> 4096 12.6 / 12.4, 9 tokens 11.2 / 12.4;
+// 16 x 3584 -> 4416 (a second workgroup on a few CUs) 17.6 / 12.4; 9 x 2560 ->
+// 8192 17.3 / 18.4 with the argmax; 16 x 9728 -> 2560 22.4 / 16.3; 11 x 9792 ->
+// 2112 (dot products) 28.7 / 15.7.
 GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, int mode, int may) {
   constexpr int kCUs = 256;
   constexpr int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
@@ -976,12 +980,9 @@ GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, int mode, int may
   constexpr double kReduce = 0.54, kPerSplit = 0.26;           // us
   constexpr double kDown = 10.74, kTBase = 1.10, kTArea = 3.03;  // us; per 16 ranks, and more for 256 x 256 outputs
   constexpr double kReadWgs = 184;  // fewer workgroups have too few bytes in flight
-  constexpr int64_t kGemvMaxWeights = 24000000;
   const int n_kt = k_dim / BK;
   GemmPlan best{-1, 1, 0};
-  if (n_tok <= kGemvDotMaxTok ||
-      (n_tok <= kGemvMaxTok && (!(may & kMaySplit) || (int64_t)n_out * k_dim < kGemvMaxWeights)))
-    return best;
+  if (n_tok <= kGemvDotMaxTok || (n_tok <= kGemvMaxTok && !(may & kMaySplit))) return best;
   const double read_w = (double)n_out * k_dim * 2 / kReadW;
   double best_t = 0.0;
   for (int i = 0; i < kNumTiles; ++i) {
@@ -1009,6 +1010,11 @@ GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, int mode, int may
         best_t = t;
       }
     }
+  }
+  if (n_tok <= kGemvMaxTok) {
+    const double gemv_t = k_dim % 128 == 0 ? 4.0 + (1.45e-3 + 3.4e-5 * n_tok) * k_dim * ((n_out + 4095) / 4096)
+                                           : 2.8 + 0.17 * n_tok + 4.4e-4 * n_out + k_dim * std::max(8.8e-5 * n_tok, 7.6e-7 * n_out);
+    if (gemv_t <= best_t) best = GemmPlan{-1, 1, 0};
   }
   return best;
 }
