@@ -886,11 +886,11 @@ struct Tile {
   double kt, first, round, idle, fuse;
 };
 constexpr Tile kTiles[] = {
-    {256, 256, 1.615, 8.6, 7.6, 0.39, 0},    {256, 192, 1.239, 10.0, 5.7, 0.39, 0},   {128, 256, 0.923, 6.4, 3.9, 0.37, 0},
-    {128, 128, 0.559, 5.8, 1.8, 0.25, 0},    {128, 64, 0.351, 6.5, 4.0, 0.29, 0},     {128, 128, 0.592, 6.8, 4.4, 0.16, 0.21},
-    {64, 96, 0.340, 5.4, 3.1, 0.24, 0.09},   {64, 64, 0.253, 5.3, 2.5, 0.30, 0.30},   {128, 192, 0.703, 7.3, 3.3, 0.40, 0.24},
-    {128, 96, 0.394, 7.6, 4.7, 0.32, 0.26},  {32, 128, 0.360, 6.2, 0.6, 0.45, 0},     {32, 64, 0.256, 5.3, 2.1, 0.36, 0},
-    {128, 256, 0.908, 9.9, 4.0, 0.36, 0.20}};
+    {256, 256, 1.614, 8.7, 7.0, 0.36, 0},    {256, 192, 1.246, 10.4, 5.8, 0.44, 0},   {128, 256, 0.923, 6.4, 3.2, 0.37, 0},
+    {128, 128, 0.555, 5.7, 1.1, 0.22, 0},    {128, 64, 0.349, 6.4, 3.6, 0.26, 0},     {128, 128, 0.588, 6.7, 4.3, 0.14, 0.21},
+    {64, 96, 0.344, 5.3, 3.2, 0.24, 0.08},   {64, 64, 0.251, 5.3, 2.5, 0.31, 0.32},   {128, 192, 0.706, 6.9, 3.8, 0.36, 0.22},
+    {128, 96, 0.397, 7.6, 4.5, 0.35, 0.26},  {32, 128, 0.357, 6.2, 0.6, 0.45, 0},     {32, 64, 0.254, 5.3, 2.2, 0.36, 0},
+    {128, 256, 0.910, 10.6, 3.9, 0.39, 0.19}};
 constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
 hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, const uint16_t* w, int n_tok, int n_out,
@@ -935,11 +935,11 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 
 // Tile and key split of a product: the least of a cost model over the tiles
 // and splits.  One workgroup per CU at a time, in rounds of 256; the k-tiles'
-// time and that of reading W from memory (8.08 TB/s, less with few workgroups)
+// time and that of reading W from memory (8.12 TB/s, less with few workgroups)
 // are added as squares.
 // With kMaySplit, and when a tile's workgroups would leave CUs idle, the k
 // range may be split across workgroups: shorter k-loops, paid for by the fp32
-// partials (split * M * N * 8 bytes written and read at 7.44 TB/s) and the
+// partials (split * M * N * 8 bytes written and read at 7.47 TB/s) and the
 // reduce launch.  A low-rank term that the tile does not compute itself costs
 // the down-projection's launch and, per 16 ranks, the epilogue of each round.
 // With one the small read-ahead tiles are left out: their few waves would each
@@ -949,7 +949,7 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 // would.  Ties go to the earlier tile and to no split.
 //
 // All tiles are on one scale: the constants are fitted together to every tile
-// and split of 2,600 shapes (the model's products and generic ones, 9 to 9,000
+// and split of 3,000 shapes (the model's products and generic ones, 9 to 16,000
 // tokens, ranks 0 to 64; weights read from memory), for the plan they choose to
 // be as near the fastest as the form allows: within 1 % of it in nine of ten of
 // the model's shapes, within 2 % of generic ones.  Two scales, one of them an
@@ -962,7 +962,8 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 // 30.1 (128 x 128) / 25.8 (its read-ahead form).  128 x 256 has both forms: the
 // one that computes t saves the down-projection's launch where k is short or the
 // rounds are few (1152 x 2560 -> 6144 at rank 16 52.7, read-ahead 57.2; 410 x
-// 576 -> 10496 18.5 / 24.8), the read-ahead one is faster without a low-rank term.
+// 576 -> 10496 18.5 / 24.8); a plain product takes the read-ahead one alone (4160
+// x 12288 -> 4096 556 / 466).
 //
 // The GEMV streams W (tile -1) up to kGemvDotMaxTok tokens, up to kGemvMaxTok
 // without a split, and up to kGemvMaxTok where it costs less.  Its matrix-core
@@ -976,10 +977,10 @@ hipError_t launch_tile(int tile, int kt_split, int grid, const uint16_t* x, cons
 GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, int mode, int may) {
   constexpr int kCUs = 256;
   constexpr int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
-  constexpr double kReadW = 8.08e6, kPartials = 7.44e6;        // bytes per us
-  constexpr double kReduce = 0.54, kPerSplit = 0.26;           // us
-  constexpr double kDown = 10.74, kTBase = 1.10, kTArea = 3.03;  // us; per 16 ranks, and more for 256 x 256 outputs
-  constexpr double kReadWgs = 184;  // fewer workgroups have too few bytes in flight
+  constexpr double kReadW = 8.12e6, kPartials = 7.47e6;        // bytes per us
+  constexpr double kReduce = 0.59, kPerSplit = 0.26;           // us
+  constexpr double kDown = 10.98, kTBase = 1.19, kTArea = 2.88;  // us; per 16 ranks, and more for 256 x 256 outputs
+  constexpr double kReadWgs = 185;  // fewer workgroups have too few bytes in flight
   const int n_kt = k_dim / BK;
   GemmPlan best{-1, 1, 0};
   if (n_tok <= kGemvDotMaxTok || (n_tok <= kGemvMaxTok && !(may & kMaySplit))) return best;
@@ -991,6 +992,7 @@ GemmPlan plan_gemm(int n_tok, int n_out, int k_dim, int r_pad, int mode, int may
     if (tl.bm != 32 && mode == kEpiF32 && n_tok <= kGemvMaxTok) continue;
     if (r_pad > 0 && tl.fuse == 0 && (!(may & kMayDown) || tl.bm * tl.bn <= 128 * 128)) continue;
     const bool fused = r_pad > 0 && r_pad <= kGemmFusedLoraMaxRank && tl.fuse > 0;
+    if (tl.bm * tl.bn == 128 * 256 && tl.fuse > 0 && !fused) continue;  // its read-ahead form
     const int64_t tiles = (int64_t)((n_tok + tl.bm - 1) / tl.bm) * (n_out / tl.bn);
     for (int s : kSplits) {
       // splits only add workgroups where the tiles alone leave CUs idle

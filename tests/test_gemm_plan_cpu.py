@@ -33,6 +33,9 @@ def _dims(tile):
     (512, 12288, 4096, 0, True, {"128x256a/4": 63.7, "128x64a/1": 80.1}),
     (1152, 2560, 2560, 0, True, {"128x128a/1": 25.8, "128x128/1": 30.1}),
     (65, 4096, 24576, 0, True, {"128x96k/1": 44.4, "128x128a/1": 46.1, "128x192k/2": 49.0}),
+    (4160, 12288, 4096, 0, True, {"128x256a/1": 466, "128x256/1": 556}),
+    (8256, 12288, 4096, 0, True, {"128x256a/1": 851, "256x256a/1": 913}),
+    (13120, 9728, 2560, 0, True, {"128x256a/1": 672, "256x256a/1": 734}),
     (7168, 2560, 6144, 0, False, {"256x256a/1": 206.9, "256x192a/1": 214.9, "128x192k/1": 233.7}),
     (5120, 2560, 6144, 16, False, {"256x256a/1": 160.6, "128x192k/1": 192.6}),
     (8192, 2560, 6144, 32, False, {"256x256a/1": 259.0, "256x192a/1": 274.4, "128x192k/1": 319.6}),
