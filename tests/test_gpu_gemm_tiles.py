@@ -130,7 +130,7 @@ def test_lm_head_tiles(n, H, V, plan):
 @pytest.mark.parametrize("T,H,rank,tile,down", [
     (1100, 2560, 33, "128x256a", True), (2500, 4096, 0, "256x256a", False), (2500, 4096, 16, "256x256a", True),
     (1500, 4096, 64, "256x192a", True),    # its 96-wide waves straddle the last adapted column
-    (1152, 2560, 16, "128x256", False), (1152, 4096, 16, "128x256a", True), (3500, 2560, 32, "256x192a", True),
+    (1152, 2560, 16, "128x256", False), (1025, 2560, 32, "128x256", False), (1152, 4096, 16, "128x256a", True), (3500, 2560, 32, "256x192a", True),
     (300, 4096, 64, "128x96k", True), (257, 2560, 0, "128x96k", False), (600, 2560, 16, "128x128", False),
     (900, 2560, 32, "128x192k", False), (150, 2560, 8, "64x96", False), (40, 4096, 64, "64x64", True),
 ])
