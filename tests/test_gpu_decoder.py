@@ -99,10 +99,10 @@ def test_rms_norm_rows(H, n, rows):
     (300, 4096, 2560, "separate"),   # o_proj of the 4B stack (K = Hq d), ragged tokens
     (256, 9728, 2560, "inplace"),    # down_proj of the 4B stack, residual read and written in place
     (513, 12288, 4096, "inplace"),   # down_proj of the 8B stack
-    # 6144 outputs, where the tile plan takes the two-k-group kernel from 129 tokens on:
+    # 6144 outputs: the two-k-group kernel from 129 to 512 tokens, read-ahead below
     (450, 4096, 6144, "none"),       # 128 x 96 tile, ragged last token tile
     (256, 4096, 6144, "separate"),   # 128 x 96 tile in 2 key splits (fp32 partials + reduce)
-    (96, 4096, 6144, "inplace"),     # 64 x 96 tile in 2 key splits
+    (96, 4096, 6144, "inplace"),     # read-ahead 128 x 128 tile in 4 key splits
 ])
 def test_linear_parity(T, K, N, res):
     _say(f"linear T={T} K={K} N={N} residual={res}")
